@@ -67,29 +67,31 @@ def encoder_roofline(h, prec: str, M: int, R: int, S: int, T: int, K: int, P: in
                      traffic_bytes=None) -> dict:
     """Roofline of one encoder launch over P patches that took enc_s seconds.
 
-    frac counts the arithmetic the encoder itself performs: the FP32 encoder splits the
-    angle DFT by harmonic parity for even R; the 16-bit encoder forms the whole DFT in 16-bit
-    (its FP32 re-score of candidates is data-dependent and not counted).  Beside it: the same
+    frac counts the arithmetic the encoder itself performs: the FP32 tiles split the
+    angle DFT by harmonic parity for even R; the screened form (16-bit handles, and FP32 handles
+    unless a tile is asked for) forms the whole DFT in 16-bit
+    (its FP32 scores of candidates are data-dependent and not counted).  Beside it: the same
     work with the direct R-angle DFT (what the split saves is counted as if done), and the
     matrix-core work actually executed (padding and recomputation included).
     """
     from paper_1806_04374_amd import rsc
-    split = prec == "fp32" and R % 2 == 0
+    tile_used, mfma_pp = rsc.rsc_encode_info(h, K)
+    screened = prec != "fp32" or tile_used == "auto"
+    split = not screened and R % 2 == 0
     own = encode_flops_per_patch(M, R, S, T, K, split=split) * P
     direct = encode_flops_per_patch(M, R, S, T, K, split=False) * P
-    tile_used, mfma_pp = rsc.rsc_encode_info(h, K)
-    peak = FP32_MFMA_PEAK if prec == "fp32" else HALF_MFMA_PEAK
-    out = {"kernel": "encode_kernel" if prec == "fp32" else "encode_lp_kernel", "bound": "mfma",
+    peak = HALF_MFMA_PEAK if screened else FP32_MFMA_PEAK
+    out = {"kernel": "encode_screen_kernel" if screened else "encode_kernel", "bound": "mfma",
            "achieved": own / enc_s / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s", "frac": own / enc_s / peak,
            "traffic": traffic_bytes, "algorithmic_flops_per_launch": own, "dft_split": split,
            "launch_ms": enc_s * 1e3,
            "frac_direct_dft_equivalent": direct / enc_s / peak,
            "executed_mfma_tflops": mfma_pp * P / enc_s / 1e12, "executed_mfma_frac": mfma_pp * P / enc_s / peak,
            "tile": tile_used}
-    if prec != "fp32":
+    if screened:
         # the 16-bit matrix work is a small part of the launch: the per-atom maxima over the
         # angles (vector instructions) and the FP32 re-score of candidates bound it
-        out["limited_by"] = "vector issue (per-atom angle maxima) and the FP32 re-score, not the 16-bit matrix peak"
+        out["limited_by"] = "vector issue (per-atom angle maxima, FP32 scores and least squares), not the 16-bit matrix peak"
     return out
 
 
@@ -697,12 +699,14 @@ def run_texture(args, dev):
         parts["histogram_nn"].append(e[2].elapsed_time(e[3]))
     # dominant kernel: the encoder, C launches per step (events around rsc_classify)
     cls_ms = float(np.median(parts["classify"]))
+    screened = rsc.rsc_encode_info(clf.handles[0], K)[0] == "auto"
     if annular:
         Sk = [sum(1 for t in proj.Ts if t >= k) for k in range(max(proj.Ts) + 1)]
         flops = annular_flops_per_patch(Sk, w["M"], R, K) * P * C
     else:
-        flops = encode_flops_per_patch(w["M"], R, g.S, g.T, K, split=args.prec == "fp32" and R % 2 == 0) * P * C
-    peak = FP32_MFMA_PEAK if args.prec == "fp32" else HALF_MFMA_PEAK
+        split = args.prec == "fp32" and R % 2 == 0 and not screened
+        flops = encode_flops_per_patch(w["M"], R, g.S, g.T, K, split=split) * P * C
+    peak = HALF_MFMA_PEAK if args.prec != "fp32" or screened else FP32_MFMA_PEAK
     images = batches[0][0].n
     out = {
         "metric": "texture windows classified per second (each coded against all C class dictionaries)",
@@ -831,6 +835,8 @@ def run_annular(args, dev):
     Sk = [sum(1 for t in Ts if t >= k) for k in range(max(Ts) + 1)]
     own = annular_flops_per_patch(Sk, M, R, K) * P
     tile_used, mfma_pp = rsc.rsc_encode_info(h, K)
+    screened = tile_used == "auto"
+    peak = HALF_MFMA_PEAK if screened else FP32_MFMA_PEAK
     out = {
         "metric": METRIC, "value": P / (ms * 1e-3), "unit": "patches/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "p50_ms": float(np.percentile(step_ms, 50)),
@@ -839,10 +845,11 @@ def run_annular(args, dev):
         "config": {"workload": f"annular: {P} {N}x{N} patches in the paper's annular basis (T_s = {Ts}, B = {h.B}), "
                                f"M={M}, K={K}, R={R}", "P": P, "N": N, "B": h.B, "M": M, "K": K, "R": R},
         "kernels_ms": {"project_mean": float(np.mean([a.elapsed_time(b) for a, b, _ in ev])), "encode_mean": enc},
-        "roofline": {"kernel": "encode16_kernel (annular layout)", "bound": "mfma",
-                     "achieved": own / (enc * 1e-3) / 1e12, "peak": FP32_MFMA_PEAK / 1e12, "unit": "TFLOP/s",
-                     "frac": own / (enc * 1e-3) / FP32_MFMA_PEAK, "algorithmic_flops_per_launch": own,
-                     "executed_mfma_frac": mfma_pp * P / (enc * 1e-3) / FP32_MFMA_PEAK, "tile": tile_used,
+        "roofline": {"kernel": f"{'encode_screen_kernel' if screened else 'encode16_kernel'} (annular layout)",
+                     "bound": "mfma",
+                     "achieved": own / (enc * 1e-3) / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
+                     "frac": own / (enc * 1e-3) / peak, "algorithmic_flops_per_launch": own,
+                     "executed_mfma_frac": mfma_pp * P / (enc * 1e-3) / peak, "tile": tile_used,
                      "traffic": None},
         "cpu_baseline": None,
     }

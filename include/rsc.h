@@ -59,15 +59,17 @@ typedef enum {
 } rsc_status;
 
 typedef enum {
-  RSC_FP32 = 0,            /* projection and correlation in FP32 on MFMA */
+  RSC_FP32 = 0,            /* projection, selection and least squares in FP32 */
   RSC_BF16 = 1,            /* correlation operands in BF16, FP32 accumulation, FP32 re-score */
   RSC_FP16 = 2             /* correlation operands in FP16, FP32 accumulation, FP32 re-score */
 } rsc_precision;
 
-/* Tile shape of the encoder (both give identical codes up to FP32 rounding order). */
+/* Form of the FP32 encoder (all give identical codes up to FP32 rounding order). */
 typedef enum {
-  RSC_TILE_AUTO = 0,       /* the library's choice: RSC_TILE_32 where it is compiled and
-                              R > 32, else RSC_TILE_16 */
+  RSC_TILE_AUTO = 0,       /* the library's choice: the screened form (see rsc_omp_encode) for
+                              the 11x11 and 15x15 grids and the annular basis at N = 11 with
+                              M <= 128 and R <= 64 where its tables fit a CU's LDS; else
+                              RSC_TILE_32 where it is compiled and R > 32, else RSC_TILE_16 */
   RSC_TILE_16 = 1,         /* 16 patches x 8 atoms per MFMA tile (v_mfma_f32_16x16x4f32) */
   RSC_TILE_32 = 2          /* 32 patches x 16 atoms per MFMA tile (v_mfma_f32_32x32x2f32);
                               S = T = 5, K <= 4 and R <= 64 only */
@@ -214,11 +216,12 @@ rsc_status rsc_set_launch(rsc_handle* h, rsc_tile tile, int blocks_per_cu);
 
 /*
  * The encoder kernel rsc_omp_encode would run for K on this handle: its tile shape
- * (RSC_TILE_16 or RSC_TILE_32, after resolving RSC_TILE_AUTO and fallbacks) and the
- * matrix-core floating-point operations it executes per patch when all K steps run
- * (padding included).  Either output pointer may be NULL.  For BF16 / FP16 handles
- * the count covers the 16-bit instructions only (the FP32 re-score of candidates
- * depends on the data; see rsc_precision_stats) and the tile is RSC_TILE_32.
+ * (RSC_TILE_16 or RSC_TILE_32 after resolving fallbacks; RSC_TILE_AUTO for the screened form of
+ * an FP32 handle) and the matrix-core floating-point operations it executes per patch when
+ * all K steps run (padding included).  Either output pointer may be NULL.  For the screened
+ * form and BF16 / FP16 handles the count covers the 16-bit instructions only (the FP32 scores
+ * of candidates depend on the data; see rsc_precision_stats); the tile of the latter is
+ * RSC_TILE_32.
  */
 rsc_status rsc_encode_info(const rsc_handle* h, int K, int* tile, double* mfma_flops_per_patch);
 
@@ -277,12 +280,15 @@ rsc_status rsc_encode_workspace_size(const rsc_handle* h, int64_t P, int K, size
  *   resid2       device [P] float32 squared hat-domain residual norm, or NULL
  * Requires rsc_set_dictionary first (else RSC_E_NOT_READY).
  *
- * BF16 / FP16 handles: the correlations of every (atom, angle) are formed with
+ * The screened form (BF16 / FP16 handles in their format; FP32 handles under RSC_TILE_AUTO with
+ * FP16 operands): the correlations of every (atom, angle) are formed with
  * 16-bit operands and FP32 accumulation; every atom whose 16-bit maximum over the
  * angles lies within 8.5u ||residual|| of the largest one (u = 2^-8 for BF16, 2^-11
  * for FP16; above twice a worst-case bound, 4.02u ||residual||, on the 16-bit error of
  * a score, so the atom with the exact maximum is always among them) is re-scored over
- * all angles in FP32, and the selection is taken from the FP32 scores.  BF16 handles
+ * all angles in FP32, and the selection is taken from the FP32 scores.  So the screen only
+ * leaves out atoms that cannot win, and the selection is that of FP32 scores of every atom; the
+ * least squares, the residual and the outputs are FP32 as in the other forms.  BF16 handles
  * re-score the atom with the largest 16-bit maximum first and then only the candidates
  * whose 16-bit maximum reaches its FP32 maximum minus 4.25u ||residual|| (the atom with
  * the largest FP32 maximum always does).

@@ -27,8 +27,12 @@ SOURCES = [
     ("rsc_project.hip", "hip"),
     ("rsc_encode.hip", "hip"),
     ("rsc_encode_annular.hip", "hip"),
-    ("rsc_encode_lp.hip", "hip"),
+    ("rsc_encode_screen.hip", "hip"),
+    ("rsc_encode_screen11.hip", "hip"),
+    ("rsc_encode_screen15.hip", "hip"),
+    ("rsc_encode_screen_bf16.hip", "hip"),
     ("rsc_synth.hip", "hip"),
+    ("rsc_dict.hip", "hip"),
     ("rsc_images.hip", "hip"),
     ("rsc_rksvd.hip", "hip"),
     ("rsc_classify.hip", "hip"),

@@ -11,6 +11,7 @@
 
 #include "rsc.h"
 #include "rsc_internal.h"
+#include "rsc_screen.h"
 
 // One of the two device arenas that hold a handle's dictionary tables.  Uploads go to the
 // arena that is not bound, so tables that launches in flight still read are never
@@ -159,21 +160,33 @@ rsc_status upload(X*& dst, const std::vector<X>& src, const char* what) {
   return RSC_OK;
 }
 
-// Packs host tables into one staging buffer at 256-byte aligned offsets; bind() then points
-// each registered device pointer into the arena (nullptr for an empty table).
+// Lays a handle's dictionary tables out in one device allocation at 256-byte aligned offsets:
+// tables computed on the host first (packed into one staging buffer), then those a kernel
+// fills.  bind() points each registered device pointer into it (nullptr for an empty table).
 struct Arena {
   std::vector<char> staging;
+  size_t total = 0;
   std::vector<std::pair<void**, size_t>> slots;  // (pointer to set, offset), offset ~0 for empty
   template <class X>
-  void add(X*& dst, const std::vector<X>& src) {
-    if (src.empty()) {
+  void add(X*& dst, const X* src, size_t n) {
+    if (n == 0) {
       slots.emplace_back(reinterpret_cast<void**>(&dst), ~size_t(0));
       return;
     }
     const size_t off = (staging.size() + 255) & ~size_t(255);
-    staging.resize(off + src.size() * sizeof(X));
-    std::memcpy(staging.data() + off, src.data(), src.size() * sizeof(X));
+    staging.resize(off + n * sizeof(X));
+    std::memcpy(staging.data() + off, src, n * sizeof(X));
     slots.emplace_back(reinterpret_cast<void**>(&dst), off);
+    total = staging.size();
+  }
+  template <class X>
+  void add(X*& dst, const std::vector<X>& src) { add(dst, src.data(), src.size()); }
+  // after the last add(): n entries left to a kernel
+  template <class X>
+  void reserve(X*& dst, size_t n) {
+    const size_t off = (total + 255) & ~size_t(255);
+    slots.emplace_back(reinterpret_cast<void**>(&dst), n == 0 ? ~size_t(0) : off);
+    if (n) total = off + n * sizeof(X);
   }
   void bind(char* base) {
     for (auto& sl : slots) *sl.first = (base && sl.second != ~size_t(0)) ? base + sl.second : nullptr;
@@ -550,41 +563,17 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
     if (std::fabs(1.0 - std::sqrt(n2)) > 1e-5)
       return fail(RSC_E_INVALID, "dictionary row " + std::to_string(m) + " is not unit norm");
   }
-  const int NG = (M + 15) / 16;
-  const int K0 = rsc::k0_steps(S), NKS = rsc::stage1_steps(S, T), NQ = T + 1;
-  auto D = [&](int m, int c) -> float { return m < M ? d_hat[size_t(m) * B + c] : 0.f; };
-  // 32x32 tiles, stage-1 operand: row 8i + j (j < 4) gives Re C_k of atom 16g + 4i + j and
-  // row 8i + 4 + j its Im C_k, so that the accumulator register of an atom holds its Re C_k
-  // in the low half-wave and its Im C_k in the high one; the two contraction lanes of a
-  // step are (Re, Im) of one profile (k >= 1) or two consecutive profiles (k = 0, where
-  // the Im rows are zero).
-  std::vector<float> dictA;
-  if (S == 5 && T == 5) {
-    dictA.assign(size_t(NG) * NKS * 64, 0.f);
-    for (int g = 0; g < NG; ++g)
-      for (int ks = 0; ks < NKS; ++ks)
-        for (int l = 0; l < 64; ++l) {
-          const int row = l % 32, hh = l / 32, a = 4 * (row / 8) + row % 4, m = 16 * g + a;
-          const bool im_row = (row / 4) % 2 == 1;
-          float v = 0.f;
-          if (ks < K0) {
-            const int s = 2 * ks + hh;
-            if (!im_row && s < S) v = D(m, s);
-          } else {
-            const int q = ks - K0, k = 1 + q / S, s = q % S, base = S + 2 * S * (k - 1);
-            const float re = D(m, base + s), im = D(m, base + S + s);
-            if (!im_row) v = hh == 0 ? re : im;
-            else v = hh == 0 ? -im : re;
-          }
-          dictA[(size_t(g) * NKS + ks) * 64 + l] = v;
-        }
-  }
-  std::vector<float> hat(size_t(NG) * 16 * B, 0.f);
-  for (int m = 0; m < M; ++m)
-    for (int b = 0; b < B; ++b) hat[size_t(m) * B + b] = d_hat[size_t(m) * B + b];
+  const int NG = (M + 15) / 16, NQ = T + 1;
+  // cos and sin of 2 pi k r / R; every angle table below takes its entries from here
   const double two_pi = 6.283185307179586476925286766559;
-  auto cosk = [&](int k, int r) { return float(std::cos(two_pi * double(k) * double(r) / double(R))); };
-  auto sink = [&](int k, int r) { return float(std::sin(two_pi * double(k) * double(r) / double(R))); };
+  std::vector<double> cs64(size_t(2) * NQ * R);
+  for (int k = 0; k < NQ; ++k)
+    for (int r = 0; r < R; ++r) {
+      cs64[size_t(k) * R + r] = std::cos(two_pi * double(k) * double(r) / double(R));
+      cs64[size_t(NQ + k) * R + r] = std::sin(two_pi * double(k) * double(r) / double(R));
+    }
+  auto cosk = [&](int k, int r) { return float(cs64[size_t(k) * R + r]); };
+  auto sink = [&](int k, int r) { return float(cs64[size_t(NQ + k) * R + r]); };
   // 32x32 tiles, stage-2 operand (even R <= 64): row = angle r < R/2, contraction
   // lanes (cos, -sin) of one harmonic, (1, 0) for k = 0
   std::vector<float> dftA32;
@@ -634,96 +623,37 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
       cs[size_t(k) * R + r] = cosk(k, r);
       cs[size_t(NQ + k) * R + r] = sink(k, r);
     }
-  // per-pair harmonic inner products in FP64: H_0 = sum_s a_s b_s (k = 0 block),
-  // H_k = sum_s conj(a_k,s) b_k,s as (Re, Im) for k >= 1, over the sk[k] profiles (or
-  // annuli) of harmonic k, whose [Re][Im] block starts at kbase[k]
   const int HQ = 2 * T + 1;
-  std::vector<int> kbase(T + 1, 0);
-  for (int k = 1; k <= T; ++k) kbase[k] = k == 1 ? d.sk[0] : kbase[k - 1] + 2 * d.sk[k - 1];
   const bool lp = h->prec != RSC_FP32;
-  // i * d in the row layout of hat (FP32 16x16 tile): the stage-1 Im rows read it at the
-  // offsets the Re rows read d, so neither needs a sign; zero at harmonic 0, whose Im row is 0
-  std::vector<float> hatI;
-  if (!lp) {
-    hatI.assign(hat.size(), 0.f);
-    for (int m = 0; m < M; ++m)
-      for (int k = 1; k <= T; ++k) {
-        const int base = kbase[k], nk = d.sk[k];
-        for (int s = 0; s < nk; ++s) {
-          hatI[size_t(m) * B + base + s] = -D(m, base + nk + s);
-          hatI[size_t(m) * B + base + nk + s] = D(m, base + s);
-        }
-      }
-  }
-  std::vector<float> gramH(size_t(M) * M * HQ);
-  std::vector<double> gramH64(gramH.size());
-  for (int a = 0; a < M; ++a)
-    for (int bb = 0; bb < M; ++bb) {
-      float* hh = &gramH[(size_t(a) * M + bb) * HQ];
-      double h0 = 0.0;
-      for (int s = 0; s < d.sk[0]; ++s) h0 += double(D(a, s)) * double(D(bb, s));
-      hh[0] = float(h0);
-      gramH64[(size_t(a) * M + bb) * HQ] = h0;
-      for (int k = 1; k <= T; ++k) {
-        const int base = kbase[k], nk = d.sk[k];
-        double re = 0.0, im = 0.0;
-        for (int s = 0; s < nk; ++s) {
-          const double ar = D(a, base + s), ai = D(a, base + nk + s);
-          const double br = D(bb, base + s), bi = D(bb, base + nk + s);
-          re += ar * br + ai * bi;
-          im += ar * bi - ai * br;
-        }
-        hh[2 * k - 1] = float(re);
-        hh[2 * k] = float(im);
-        gramH64[(size_t(a) * M + bb) * HQ + 2 * k - 1] = re;
-        gramH64[(size_t(a) * M + bb) * HQ + 2 * k] = im;
-      }
-    }
-  // 16-bit encoder tables
-  std::vector<uint16_t> lpA, lpF16;
+  // screened encoder tables: 16-bit operands in the handle's format (FP16 for FP32 handles, whose
+  // selection and least squares stay in FP32: the screen only leaves out atoms that cannot win)
+  std::vector<uint16_t> lpF16;
   std::vector<float> lpF32;
-  std::vector<double> cs64;
   bool split = false;
-  if (lp) {
-    if (!rsc::encode_lp_supported(S, T, M, R))
-      return fail(RSC_E_UNSUPPORTED, "16-bit encoder: needs M <= 128 and R <= 64");
-    auto cvt = [&](float v) { return h->prec == RSC_BF16 ? to_bf16(v) : to_f16(v); };
-    // stage 1: lane l gives row l % 32 = (atom 4(row/8) + row%4, Re/Im = (row/4)%2) and
-    // contraction slots 8(l/32)..+7: the residual's harmonic-k block, Re parts (k = 0:
-    // even profiles) in the low half-wave, Im parts (k = 0: odd profiles) in the high
-    lpA.assign(size_t(NG) * NQ * 64 * 8, 0);
-    for (int g = 0; g < NG; ++g)
-      for (int k = 0; k < NQ; ++k)
+  const bool screened = rsc::screen_supported(d.geo, S, T, M, R);
+  if (lp && !screened) return fail(RSC_E_UNSUPPORTED, "16-bit encoder: needs M <= 128 and R <= 64");
+  const rsc_precision scr = !screened ? RSC_FP32 : lp ? h->prec : RSC_FP16;
+  size_t nlpA = 0;
+  if (screened) {
+    auto cvt = [&](float v) { return scr == RSC_BF16 ? to_bf16(v) : to_f16(v); };
+    const int OPS = rsc::screen_ops(T), AG = rsc::screen_group_atoms(T);
+    nlpA = size_t((M + AG - 1) / AG) * rsc::screen_steps(T) * 64 * 8;
+    const int RT = (R + 31) / 32;
+    // stage 2: row = angle 32t + l%32, slots k of the low half-wave cos((8o + k) theta),
+    // of the high half-wave -sin
+    lpF16.assign(size_t(OPS) * RT * 64 * 8, 0);
+    for (int o = 0; o < OPS; ++o)
+      for (int t = 0; t < RT; ++t)
         for (int l = 0; l < 64; ++l) {
-          const int row = l % 32, hh = l / 32, a = 4 * (row / 8) + row % 4, part = (row / 4) % 2;
-          const int m = 16 * g + a;
-          for (int i = 0; i < 8; ++i) {
-            float v = 0.f;
-            if (k == 0) {
-              const int s = 2 * i + hh;
-              if (part == 0 && s < S) v = D(m, s);
-            } else if (i < S) {
-              const int base = S + 2 * S * (k - 1);
-              const float re = D(m, base + i), im = D(m, base + S + i);
-              v = part == 0 ? (hh == 0 ? re : im) : (hh == 0 ? -im : re);
-            }
-            lpA[((size_t(g) * NQ + k) * 64 + l) * 8 + i] = cvt(v);
+          const int r = 32 * t + l % 32, hh = l / 32;
+          if (r >= R) continue;
+          for (int i = 0; i < 8 && 8 * o + i < NQ; ++i) {
+            const int k = 8 * o + i;
+            const float v = hh == 0 ? (k == 0 ? 1.f : cosk(k, r)) : (k == 0 ? 0.f : -sink(k, r));
+            lpF16[((size_t(o) * RT + t) * 64 + l) * 8 + i] = cvt(v);
           }
         }
-    const int RT = (R + 31) / 32;
-    // stage 2: row = angle 32t + l%32, slots k of the low half-wave cos(k theta),
-    // of the high half-wave -sin(k theta)
-    lpF16.assign(size_t(RT) * 64 * 8, 0);
-    for (int t = 0; t < RT; ++t)
-      for (int l = 0; l < 64; ++l) {
-        const int r = 32 * t + l % 32, hh = l / 32;
-        if (r >= R) continue;
-        for (int k = 0; k < NQ; ++k) {
-          const float v = hh == 0 ? (k == 0 ? 1.f : cosk(k, r)) : (k == 0 ? 0.f : -sink(k, r));
-          lpF16[(size_t(t) * 64 + l) * 8 + k] = cvt(v);
-        }
-      }
-    // FP32 re-score operand: radix-2 split (rows r < R/2) for even R in 33..64, else
+    // FP32 angle DFT operand: radix-2 split (rows r < R/2) for even R in 33..64, else
     // RT tiles of the direct DFT; contraction lanes (cos, -sin), (1, 0) for k = 0
     split = R % 2 == 0 && R > 32;
     const int FT = split ? 1 : RT, rows = split ? R / 2 : R;
@@ -736,12 +666,6 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
           lpF32[(size_t(t) * NQ + k) * 64 + l] = hh == 0 ? (k == 0 ? 1.f : cosk(k, r)) : (k == 0 ? 0.f : -sink(k, r));
       }
   }
-  cs64.resize(cs.size());
-  for (int k = 0; k < NQ; ++k)
-    for (int r = 0; r < R; ++r) {
-      cs64[size_t(k) * R + r] = std::cos(two_pi * double(k) * double(r) / double(R));
-      cs64[size_t(NQ + k) * R + r] = std::sin(two_pi * double(k) * double(r) / double(R));
-    }
   // the new tables must fit a CU's LDS; checked before the handle changes, so a refused
   // upload leaves the current dictionary in place
   rsc::DeviceTables nd = d;
@@ -749,40 +673,45 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
   nd.R = R;
   nd.NG = NG;
   nd.lpSplit = split;
-  if (lp && rsc::encode_lp_lds_bytes(nd) > 160 * 1024)
+  nd.scrPrec = scr;
+  if (lp && !rsc::screen_usable(nd, 8))
     return fail(RSC_E_UNSUPPORTED, "dictionary tables exceed the 160 KiB LDS of a CU");
   if (!lp && rsc::encode_lds_bytes(nd, RSC_TILE_16) > 160 * 1024)
     return fail(RSC_E_UNSUPPORTED, "dictionary tables exceed the 160 KiB LDS of a CU");
-  // one host staging buffer, one copy into the arena that is not bound
+  // one host staging buffer (the angle tables and the rows) and one copy into the arena that is
+  // not bound, where a kernel then builds the tables that depend on the rows
   Arena arena;
-  arena.add(d.dictA, dictA);
-  arena.add(d.dictHat, hat);
-  arena.add(d.dictHatI, hatI);
-  arena.add(d.dftA32, dftA32);
-  arena.add(d.dftA16, dftA16);
-  arena.add(d.dftA16s, dftA16s);
-  arena.add(d.cs, cs);
-  arena.add(d.gramH, gramH);
-  arena.add(d.lpA, lpA);
-  arena.add(d.lpF16, lpF16);
-  arena.add(d.lpF32, lpF32);
-  arena.add(d.gramH64, gramH64);
-  arena.add(d.cs64, cs64);
-  const size_t need = arena.staging.size();
+  float* rows = nullptr;
+  arena.add(nd.dftA32, dftA32);
+  arena.add(nd.dftA16, dftA16);
+  arena.add(nd.dftA16s, dftA16s);
+  arena.add(nd.cs, cs);
+  arena.add(nd.cs64, cs64);
+  arena.add(nd.lpF16, lpF16);
+  arena.add(nd.lpF32, lpF32);
+  arena.add(rows, d_hat, size_t(M) * B);
+  const size_t staged = arena.staging.size(), nhat = size_t(NG) * 16 * B, ngram = size_t(M) * M * HQ;
+  arena.reserve(nd.dictHat, nhat);
+  arena.reserve(nd.dictHatI, lp ? 0 : nhat);
+  arena.reserve(nd.dictA, S == 5 && T == 5 ? size_t(NG) * rsc::stage1_steps(S, T) * 64 : 0);
+  arena.reserve(nd.lpA, nlpA);
+  arena.reserve(nd.gramH, ngram);
+  arena.reserve(nd.gramH64, ngram);
+  const size_t need = arena.total;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   DictSlot& sl = h->slot[h->cur < 0 ? 0 : 1 - h->cur];
   hipError_t e = hipSuccess;
   if (sl.copied && (e = hipEventSynchronize(sl.copied)) != hipSuccess)   // staging of its last upload
     return handle_fail(h, int(e), "wait for an earlier dictionary upload");
-  if (sl.pinned_bytes < need) {
+  if (sl.pinned_bytes < staged) {
     if (sl.pinned) (void)hipHostFree(sl.pinned);
     sl.pinned = nullptr;
     sl.pinned_bytes = 0;
-    if (hipHostMalloc(&sl.pinned, need, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&sl.pinned, staged, hipHostMallocDefault) != hipSuccess) {
       sl.pinned = nullptr;
       return fail(RSC_E_NOMEM, "hipHostMalloc for the dictionary staging failed");
     }
-    sl.pinned_bytes = need;
+    sl.pinned_bytes = staged;
   }
   if (sl.bytes < need) {
     // launches in flight may still read the arena: wait for them before it is freed
@@ -799,22 +728,27 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
   }
   if (!sl.copied && (e = hipEventCreateWithFlags(&sl.copied, hipEventDisableTiming)) != hipSuccess)
     return handle_fail(h, int(e), "event creation");
-  std::memcpy(sl.pinned, arena.staging.data(), need);
+  std::memcpy(sl.pinned, arena.staging.data(), staged);
   // the copy waits for every launch that read this arena (events recorded after them)
   for (auto& u : sl.users)
     if ((e = hipStreamWaitEvent(st, u.second, 0)) != hipSuccess)
       return handle_fail(h, int(e), "stream wait before the dictionary upload");
-  if ((e = hipMemcpyAsync(sl.arena, sl.pinned, need, hipMemcpyHostToDevice, st)) != hipSuccess)
+  if ((e = hipMemcpyAsync(sl.arena, sl.pinned, staged, hipMemcpyHostToDevice, st)) != hipSuccess)
     return handle_fail(h, int(e), "dictionary upload");
+  arena.bind(static_cast<char*>(sl.arena));
+  rsc::DictBuild build{rows, M, B, T, NG * 16, {}, {}, scr == RSC_BF16, nd.dictHat, nd.dictHatI, nd.dictA, nd.lpA,
+                       nd.gramH, nd.gramH64};
+  for (int k = 0; k <= T; ++k) {
+    build.sk[k] = d.sk[k];
+    build.kbase[k + 1] = build.kbase[k] + (k == 0 ? 1 : 2) * d.sk[k];
+  }
+  if ((e = hipError_t(rsc::launch_dict_tables(build, stream))) != hipSuccess)
+    return handle_fail(h, int(e), "dictionary table launch");
   if ((e = hipEventRecord(sl.copied, st)) != hipSuccess) return handle_fail(h, int(e), "event record");
   // later launches read the new arena
-  arena.bind(static_cast<char*>(sl.arena));
-  d.M = M;
-  d.R = R;
-  d.NG = NG;
-  d.lpSplit = split;
-  d.dictArena = sl.arena;
-  d.dictArenaBytes = need;
+  nd.dictArena = sl.arena;
+  nd.dictArenaBytes = need;
+  d = nd;
   h->cur = int(&sl - h->slot);
   h->dict_stream = st;
   h->has_dict = true;
@@ -851,11 +785,15 @@ rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int 
   if (rsc_status f = dict_before(h, stream)) return f;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool lp = h->prec != RSC_FP32;
-  int tiles[2] = {lp ? RSC_TILE_32 : RSC_TILE_16, RSC_TILE_32};
+  // FP32 handles: the library's screened form (RSC_TILE_AUTO) where there is one, and otherwise
+  // every FP32 tile shape; 16-bit handles have one form
+  const bool screened = rsc::screen_usable(h->dev, K);
+  int tiles[2] = {lp ? RSC_TILE_32 : screened ? RSC_TILE_AUTO : RSC_TILE_16, RSC_TILE_32};
   const int ntiles = (!lp && rsc::tile32_usable(h->dev, K)) ? 2 : 1;
   auto run = [&](int tile) {
-    return lp ? rsc::launch_encode_lp(h->dev, h->prec, xhat, P, K, atom, angle, coef, nullptr, stream)
-              : rsc::launch_encode(h->dev, tile, xhat, P, K, atom, angle, coef, nullptr, stream);
+    return lp || (screened && tile == RSC_TILE_AUTO)
+               ? rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, nullptr, stream)
+               : rsc::launch_encode(h->dev, tile, xhat, P, K, atom, angle, coef, nullptr, stream);
   };
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return fail(RSC_E_DEVICE, "hipEventCreate failed");
@@ -921,13 +859,20 @@ int encoder_tile(const rsc_handle* h, int K) {
   return want32 && rsc::tile32_usable(h->dev, K) ? RSC_TILE_32 : RSC_TILE_16;
 }
 
+// Whether the pursuit of K atoms runs the screened encoder: every 16-bit handle, and FP32 handles
+// under RSC_TILE_AUTO where it is compiled (M <= 128, R <= 64, its tables within the LDS).  It
+// depends on the handle and K only, never on P, so a patch's code does not depend on its launch.
+bool encoder_screened(const rsc_handle* h, int K) {
+  return (h->prec != RSC_FP32 || h->tile == RSC_TILE_AUTO) && rsc::screen_usable(h->dev, K);
+}
+
 rsc_status rsc_encode_info(const rsc_handle* h, int K, int* tile, double* mfma_flops_per_patch) {
   if (!h) return fail(RSC_E_INVALID, "handle is NULL");
   if (!h->has_dict) return fail(RSC_E_NOT_READY, "no dictionary loaded");
   if (K < 1 || K > 8 || K > h->dev.B) return fail(RSC_E_INVALID, "K must be in 1..min(8, B)");
-  if (h->prec != RSC_FP32) {
-    if (tile) *tile = RSC_TILE_32;
-    if (mfma_flops_per_patch) *mfma_flops_per_patch = rsc::encode_lp_mfma_flops_per_patch(h->dev, K);
+  if (encoder_screened(h, K)) {
+    if (tile) *tile = h->prec == RSC_FP32 ? RSC_TILE_AUTO : RSC_TILE_32;
+    if (mfma_flops_per_patch) *mfma_flops_per_patch = rsc::screen_mfma_flops_per_patch(h->dev, K);
     return ok();
   }
   const int t = encoder_tile(h, K);
@@ -968,9 +913,9 @@ rsc_status rsc_omp_encode(const rsc_handle* h, const float* xhat, int64_t P, int
   if (P == 0) return ok();
   if (!xhat || !atom || !angle || !coef) return fail(RSC_E_INVALID, "null device pointer");
   if (rsc_status f = check_fault(h)) return f;
-  if (h->prec != RSC_FP32)
+  if (encoder_screened(h, K))
     return dict_launch(h, stream, "encode launch", [&] {
-      return rsc::launch_encode_lp(h->dev, h->prec, xhat, P, K, atom, angle, coef, resid2, stream);
+      return rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, resid2, stream);
     });
   const int tile = encoder_tile(h, K);
   return dict_launch(h, stream, "encode launch", [&] {

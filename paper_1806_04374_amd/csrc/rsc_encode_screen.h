@@ -1,0 +1,511 @@
+// Rotational OMP with a 16-bit screen and FP32 selection (Fig. 2 with rotations replaced by
+// steering: Sec. II-C, eq. (8); Sec. II-E step 3).
+//
+// Each wave owns 32 patches (MFMA columns).  Per pursuit step:
+//   screen, v_mfma_f32_32x32x16_{f16,bf16}: stage 1 forms C_k = sum_s conj(d_{m,s,k}) x_{s,k}
+//     of a group of atoms (rsc_screen.h), stage 2 the angle DFT per atom and 32 angles.  Only
+//     the largest |score| of each atom over its angles is kept, and from it which atoms are
+//     candidates: those within 8.5u ||r|| of the largest one (u: unit roundoff of the format).
+//     Per harmonic k, rounding the atom and the residual moves C_k by at most (2u + u^2)
+//     sum_s |d_{k,s}| |x_{k,s}| (complex magnitudes), and rounding the stage-2 operand C_k and
+//     (cos, -sin) moves the term cos Re C_k - sin Im C_k by at most (2u + u^2) |C_k|
+//     (Cauchy-Schwarz on the 2-vectors).  Summed over k with unit-norm atoms (Cauchy-Schwarz
+//     again), a 16-bit score is within (2u + u^2)(1 + (1 + u)^2) ||r|| = 4.02u ||r|| (BF16;
+//     less for FP16) of the exact one; FP32 accumulation adds below 1e-3 of that.  So the
+//     atom with the exact maximum lies within twice that (8.05u ||r||) of the largest 16-bit
+//     maximum, and the window keeps it.  FP16 residuals are first scaled by a power of two to
+//     a norm in [0.5, 1), which keeps every coordinate that matters out of the subnormal
+//     range; a residual too small for its norm to be exact to a few percent takes every atom.
+//   selection in FP32: every candidate's scores are formed in FP32 (C_k from the packed
+//     dictionary, the angle DFT on v_mfma_f32_32x32x2f32), and the atom and angle of the
+//     largest one win; equal maxima go to the smaller atom, then the smaller angle.  The
+//     screen only leaves out atoms that cannot win, so the selection is the one that FP32
+//     scores of every atom give.
+//   BF16 filter: a BF16 window holds several atoms per step, and a wave loops over its patches'
+//     largest candidate count.  So the atom with the largest 16-bit maximum is scored first, and
+//     of the others only those are kept whose 16-bit maximum reaches its FP32 maximum minus the
+//     error bound (4.02u ||r||, taken as 4.25u): the atom with the largest FP32 maximum E has a
+//     16-bit maximum of at least E - 4.02u ||r||, and E is at least the first one's.  The 16-bit
+//     maxima are kept for this as FP16 fractions of ||r|| in private memory, which is read only
+//     for candidates, with a margin of 2^-10 for their rounding.  FP16's window holds about one
+//     atom, and the bookkeeping would cost more than it saves.
+//   least squares and residual update in FP32 (ls_update), as in the FP32 encoders.
+//
+// What bounds it: vector issue.  A wave's maxima over 64 angles cost 16 three-way maxima per
+// atom for 32 patches, and the 16-bit products take as many cycles on the matrix cores, so
+// two waves per SIMD hide one behind the other as far as registers allow: the least-squares
+// state waits in LDS while the screen runs, which is what brings the kernel to 256 registers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rsc_device.h"
+#include "rsc_internal.h"
+#include "rsc_launch.h"
+#include "rsc_lp.h"
+#include "rsc_screen.h"
+
+namespace rsc {
+namespace screen {
+
+struct ScreenParams {
+  const float* xhat;
+  int64_t P;
+  int K, M, R;
+  const uint4* dictA;      // stage-1 operand [NG][NJ][64] x 8 16-bit values
+  const float* dictHat;    // [>= NG AG][B]
+  const uint4* dft16;      // stage-2 operand [OPS][RT][64] x 8 16-bit values
+  const float* dft32;      // FP32 angle DFT [FT][NQ][64]
+  const float* cs;         // [2][NQ][R]
+  const float* gramH;      // [M][M][2T+1]
+  const double* gramH64;   // [M][M][2T+1]
+  const double* cs64;      // [2][NQ][R]
+  int32_t* atom;
+  int32_t* angle;
+  float* coef;
+  float* resid2;
+  unsigned long long* stats;   // [4], see rsc_precision_stats
+  float cond_max;              // least squares in FP64 beyond this bound (ls_update)
+  bool count;                  // whether candidates are counted (16-bit handles)
+};
+
+// The least-squares state of the wave's 32 patches in LDS: float4 q of patch col at
+// st[q * 32 + col].  Both half-waves hold the same values; the low one writes.
+template <int KMAX>
+struct StateIo {
+  static constexpr int N4 = screen_state_f4(KMAX);
+  template <class F>
+  __device__ __forceinline__ static void each(PursuitState<KMAX>& st, LsState<KMAX>& ls, F f) {
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i)
+#pragma unroll
+      for (int j = 0; j < i; ++j) f(n++, st.L[i][j]);
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) f(n++, ls.Ld[i]);
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) f(n++, st.bv[i]);
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) f(n++, st.cf[i]);
+  }
+  __device__ __forceinline__ static void save(float4* mem, int lane, PursuitState<KMAX>& st, LsState<KMAX>& ls) {
+    float v[4 * N4];
+    zero(v);
+    each(st, ls, [&](int n, float& x) { v[n] = x; });
+    if (lane < 32) {
+#pragma unroll
+      for (int q = 0; q < N4; ++q) mem[q * 32 + lane] = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    }
+  }
+  __device__ __forceinline__ static void load(const float4* mem, int col, PursuitState<KMAX>& st, LsState<KMAX>& ls) {
+    float v[4 * N4];
+#pragma unroll
+    for (int q = 0; q < N4; ++q) {
+      const float4 w = mem[q * 32 + col];
+      v[4 * q] = w.x;
+      v[4 * q + 1] = w.y;
+      v[4 * q + 2] = w.z;
+      v[4 * q + 3] = w.w;
+    }
+    each(st, ls, [&](int n, float& x) { x = v[n]; });
+  }
+};
+
+// A patch's coordinates x [B] into the registers of its two lanes (W = 2): register j of
+// harmonic k >= 1 reads the Re part in the low half-wave and the Im part, Sk(k) further on, in
+// the high one, so each harmonic costs one address and constant offsets.  A padding register
+// of harmonic 0 reads the value that follows, harmonic 1's first, and is set to 0.
+template <class L>
+__device__ __forceinline__ void load_hat(const float* __restrict__ x, int u, bool valid, float (&res)[L::NKS]) {
+  static_assert(L::W == 2 && L::T >= 1, "two half-waves per patch");
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) res[j] = x[2 * j + u];
+  static_for<L::T>([&](auto K1) {
+    constexpr int k = decltype(K1)::value + 1;
+    const float* xk = x + (u ? L::Sk(k) : 0);
+#pragma unroll
+    for (int i = 0; i < L::Sk(k); ++i) res[L::joff(k) + i] = xk[L::base(k) + i];
+  });
+  if (L::Sk(0) % 2 == 1) res[L::J0 - 1] = u ? 0.f : res[L::J0 - 1];
+#pragma unroll
+  for (int j = 0; j < L::NKS; ++j) res[j] = valid ? res[j] : 0.f;
+}
+
+// Orders the low half-wave's LDS writes before the whole wave's reads: neither the compiler (which
+// sees a conditional store and a load of one thread) nor the hardware moves one past the other.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Bytes of the tables that a block keeps in LDS, rounded up to 16.
+__host__ __device__ constexpr size_t screen_table_bytes(int NG, int NJ, int NQ, int rows, int B, int R, int FT) {
+  return size_t(NG) * NJ * 1024 + ((sizeof(float) * (size_t(rows) * B + 2 * size_t(NQ) * R + size_t(FT) * NQ * 64) + 15) & ~size_t(15));
+}
+
+// RT: 32-angle tiles of the screen (ceil(R / 32)).  SPLIT: the FP32 scores use the radix-2
+// angle split (even R, R/2 <= 32 rows: E from even harmonics, O from odd ones, score(r) = E + O
+// and score(r + R/2) = E - O); otherwise RT tiles of the direct angle DFT.
+template <class C, int KMAX, int PREC, int RT, bool SPLIT>
+__global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm) {
+  using L = LayoutBase<C, 2>;
+  using P = Lp<PREC>;
+  using V8 = typename P::V8;
+  constexpr int NKS = L::NKS, NQ = L::NQ, B = L::B, J0 = L::J0, T = L::T;
+  constexpr int OPS = screen_ops(T), AG = screen_group_atoms(T), NJ = screen_steps(T), HA = AG / 2;
+  constexpr int FT = SPLIT ? 1 : RT;
+  static_assert(NQ <= 16, "two stage-2 operands hold 16 harmonics");
+  extern __shared__ uint4 lds4[];
+  const int R = prm.R, M = prm.M, K = prm.K, NG = (M + AG - 1) / AG, rows = NG * AG;
+  const V8* sA = reinterpret_cast<const V8*>(lds4);             // [NG][NJ][64]
+  float* sHat = reinterpret_cast<float*>(lds4 + NG * NJ * 64);  // [rows][B]
+  float* sCs = sHat + rows * B;                                 // [2][NQ][R]
+  float* sF = sCs + 2 * NQ * R;                                 // [FT][NQ][64]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = int(blockDim.x) >> 6;
+  float4* sState = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds4) + screen_table_bytes(NG, NJ, NQ, rows, B, R, FT)) +
+                   wave * (StateIo<KMAX>::N4 * 32);
+  {
+    const int nA = NG * NJ * 64, nH = rows * B, nC = 2 * NQ * R, nF = FT * NQ * 64;
+    for (int i = threadIdx.x; i < nA; i += blockDim.x) lds4[i] = prm.dictA[i];
+    for (int i = threadIdx.x; i < nH; i += blockDim.x) sHat[i] = prm.dictHat[i];
+    for (int i = threadIdx.x; i < nC; i += blockDim.x) sCs[i] = prm.cs[i];
+    for (int i = threadIdx.x; i < nF; i += blockDim.x) sF[i] = prm.dft32[i];
+  }
+  __syncthreads();
+
+  const int col = lane & 31, u = lane >> 5;
+  V8 F16[OPS][RT];
+#pragma unroll
+  for (int o = 0; o < OPS; ++o)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const uint4 w = prm.dft16[(o * RT + t) * 64 + lane];
+      __builtin_memcpy(&F16[o][t], &w, sizeof(w));
+    }
+  const LsTables tb{prm.gramH, prm.gramH64, prm.cs64, prm.xhat, M, R, prm.cond_max};
+  constexpr float wfac = 8.5f * P::unit;
+  constexpr bool kFilter = PREC == RSC_BF16;
+  constexpr float efac = 4.25f * P::unit + 0x1p-10f;
+  static_assert(!kFilter || HA == 8, "the filter keeps 8 maxima per lane and group");
+  uint4 vmax[kFilter ? 8 : 1];   // [groups] 8 FP16 fractions: this lane's maxima of the step
+  unsigned n_sel = 0, n_cand = 0, n_fp64 = 0, max_cand = 0;
+
+  // tiles go to the blocks first and then to their waves, so that a launch of few tiles
+  // spreads over the CUs
+  const int64_t nwt = (prm.P + 31) / 32;
+  for (int64_t wt = int64_t(blockIdx.x) + int64_t(gridDim.x) * wave; wt < nwt; wt += int64_t(gridDim.x) * nw) {
+    const int64_t p = wt * 32 + col;
+    const bool valid = p < prm.P;
+    float res[NKS];
+    load_hat<L>(prm.xhat + (valid ? p : prm.P - 1) * B, u, valid, res);
+    const float nx2 = norm2<L>(res);
+    PursuitState<KMAX> st;
+    init_state(st, valid);
+    LsState<KMAX> ls;
+    init_ls(ls);
+
+    for (int it = 0; it < K; ++it) {
+      const float n2 = norm2<L>(res);
+      st.active = st.active && (n2 > kTau2 * nx2);
+      if (!__any(st.active)) break;
+      StateIo<KMAX>::save(sState, lane, st, ls);
+      wave_lds_order();
+
+      // ---------------- 16-bit residual operand, one per stage-1 step (FP16: the residual
+      // scaled by 2^-e, ||r|| = f 2^e with f in [0.5, 1); the scores and the window are
+      // compared in the scaled units)
+      const float rn = sqrtf(n2);
+      int ex = 0;
+      if (PREC == RSC_FP16) (void)frexpf(rn, &ex);
+      const float sc = PREC == RSC_FP16 ? ldexpf(1.f, -ex) : 1.f;
+      V8 r16[NJ];
+      static_for<NJ>([&](auto J) {
+        constexpr int k = decltype(J)::value;
+        constexpr int c0 = k == 0 ? J0 : L::Sk(k);
+        constexpr int k2 = k + 8 < NQ ? k + 8 : 0, c1 = k + 8 < NQ ? L::Sk(k2) : 0;
+        static_assert(c0 + c1 <= 8, "a step's profiles must fit one half-wave's 8 slots");
+        float v[8];
+        zero(v);
+#pragma unroll
+        for (int i = 0; i < c0; ++i) v[i] = sc * res[L::joff(k) + i];
+#pragma unroll
+        for (int i = 0; i < c1; ++i) v[c0 + i] = sc * res[L::joff(k2) + i];
+        r16[k] = pack8<P>(v);
+      });
+      // below 1e-30 the squared norm is itself inexact: every atom is then a candidate
+      const float wnd = n2 > 1e-30f ? wfac * rn * sc : 1e30f;
+
+      // ---------------- 16-bit scores: per-atom maxima and the candidate mask
+      float vh = -1.f;          // running maximum over this half-wave's atoms
+      int va = 0;               // its atom (the first one on equal maxima; with the filter)
+      const float invn = rn > 0.f ? 1.f / (rn * sc) : 0.f;
+      uint64_t mask = 0;        // bit i: atom 2i + u is a candidate
+      for (int g = 0; g < NG; ++g) {
+        asm volatile("" ::: "memory");
+        const V8* Ag = sA + g * NJ * 64 + lane;
+        // stage 1 by pairs of steps; each pair is rounded at once into one 32-bit register
+        // (two 16-bit slots) of every row pair's stage-2 operand
+        u32x4 opk[16];
+        f32x16 zro;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zro[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int k0 = 2 * j, k1 = 2 * j + 1;
+          if (k0 >= NJ) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a) opk[a][j] = 0u;
+            continue;
+          }
+          const f32x16 a0 = P::mfma(Ag[k0 * 64], r16[k0], zro);
+          const f32x16 a1 = k1 < NJ ? P::mfma(Ag[(k1 < NJ ? k1 : k0) * 64], r16[k1 < NJ ? k1 : k0], zro) : zro;
+#pragma unroll
+          for (int a = 0; a < 16; ++a) opk[a][j] = pack2<P>(a0[a], a1[a]);
+        }
+        const int ab = AG * g;
+        // stage 2 by (atom, angle tile) units, one unit in flight: the next unit's
+        // products are issued before the current one's reduction
+        auto issue = [&](int q) {
+          const int a = q / RT, t = q % RT;
+          f32x16 s = P::mfma(F16[0][t], __builtin_bit_cast(V8, opk[a]), zro);
+          if constexpr (OPS == 2) s = P::mfma(F16[OPS - 1][t], __builtin_bit_cast(V8, opk[(a + 8) % 16]), s);
+          return s;
+        };
+        float vs[HA];         // slot i: maximum of atom ab + 2i + u over its angles
+        f32x16 cur = issue(0);
+        float part = 0.f, mprev = 0.f;
+#pragma unroll
+        for (int q = 0; q < AG * RT; ++q) {
+          const int a = q / RT, t = q % RT;
+          f32x16 nxt;
+          if (q + 1 < AG * RT) nxt = issue(q + 1);
+          if (t == 0) part = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; i += 2) part = fmaxf(fmaxf(part, fabsf(cur[i])), fabsf(cur[i + 1]));
+          if (t == RT - 1) {
+            if (a % 2 == 0) {
+              mprev = part;
+            } else {
+              // atoms a-1 and a completed across the half-waves: atom ab + a - 1 in
+              // the low half-wave, ab + a in the high one (non-negative floats as integers)
+              float m0 = mprev, m1 = part;
+              swap32(m0, m1);
+              vs[a / 2] = __uint_as_float(max(__float_as_uint(m0), __float_as_uint(m1)));
+            }
+          }
+          if (q + 1 < AG * RT) cur = nxt;
+        }
+        if (ab + AG > M) {
+#pragma unroll
+          for (int i = 0; i < HA; ++i) vs[i] = ab + 2 * i + u < M ? vs[i] : -1.f;
+        }
+        // candidates of this group against the running maximum; a rise of the maximum
+        // by more than the window drops every earlier candidate
+        float gm = vs[0];
+#pragma unroll
+        for (int i = 1; i < HA; ++i) gm = fmaxf(gm, vs[i]);
+        const float nvh = fmaxf(vh, gm), thr = nvh - wnd;
+        mask = vh < thr ? uint64_t(0) : mask;
+        const float thr0 = fmaxf(thr, 0.f);
+        unsigned gb = 0;
+#pragma unroll
+        for (int i = 0; i < HA; ++i) gb |= vs[i] >= thr0 ? (1u << i) : 0u;
+        mask |= uint64_t(gb) << (HA * g);
+        if constexpr (kFilter) {
+          int gi = HA - 1;
+#pragma unroll
+          for (int i = HA - 1; i >= 0; --i) gi = vs[i] == gm ? i : gi;
+          va = gm > vh ? ab + 2 * gi + u : va;
+          _Float16 hv[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) hv[i] = _Float16(vs[i < HA ? i : 0] * invn);
+          __builtin_memcpy(&vmax[g], hv, sizeof(uint4));
+        }
+        vh = nvh;
+      }
+      const float vo = __shfl_xor(vh, 32);
+      if (!(vh >= fmaxf(vh, vo) - wnd) || !st.active) mask = 0;
+      // with the filter: the atom of the largest 16-bit maximum (the low half-wave's on equal
+      // maxima) goes first
+      const int vao = kFilter ? __shfl_xor(va, 32) : 0;
+      const int m1 = (u == 0 ? vh >= vo : vo < vh) ? va : vao;
+      const bool has1 = st.active && fmaxf(vh, vo) >= 0.f;
+      if (kFilter && has1 && (m1 & 1) == u) mask &= ~(uint64_t(1) << (m1 >> 1));
+
+      // ---------------- FP32 scores of the candidates, in increasing atom order (after the first)
+      float best = -1.f;
+      int bm = 0;
+      unsigned nc = 0;
+      f32x16 E[FT], O;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        O[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < FT; ++t) E[t][i] = 0.f;
+      }
+      for (int pass = 0;; ++pass) {
+        int m;
+        bool has;
+        if (kFilter && pass == 0) {
+          m = m1;
+          has = has1;
+        } else {
+          const int mine = mask ? 2 * int(__builtin_ctzll(mask)) + u : 0x7fffffff;
+          m = min(mine, __shfl_xor(mine, 32));
+          has = m != 0x7fffffff;
+          if (has && mine == m) mask &= mask - 1;
+        }
+        if (!__any(has)) break;
+        nc += has ? 1 : 0;
+        const int mc = has ? m : 0;
+        float op32[NQ];
+        atom_operand<L>(sHat, mc, u, res, op32);
+        f32x16 e[FT], o;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < FT; ++t) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) e[t][i] = 0.f;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            if (SPLIT && q % 2 == 1) o = mfma32(sF[q * 64 + lane], op32[q], o);
+            else e[t] = mfma32(sF[(t * NQ + q) * 64 + lane], op32[q], e[t]);
+          }
+        }
+        float cm = 0.f;
+#pragma unroll
+        for (int t = 0; t < FT; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) cm = fmaxf(cm, SPLIT ? fabsf(e[t][i]) + fabsf(o[i]) : fabsf(e[t][i]));
+        cm = max_halves_nonneg(cm);
+        // equal maxima go to the smaller atom (without the filter the atoms come in order)
+        const bool gt = has && (cm > best || (kFilter && cm == best && mc < bm));
+        best = gt ? cm : best;
+        bm = gt ? mc : bm;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+#pragma unroll
+          for (int t = 0; t < FT; ++t) E[t][i] = gt ? e[t][i] : E[t][i];
+          if (SPLIT) O[i] = gt ? o[i] : O[i];
+        }
+        if (kFilter && pass == 0) {
+          const float thrn = has ? best / rn - efac : -2.f;
+          uint64_t mm = mask, keep = 0;
+          while (mm) {
+            const int i = int(__builtin_ctzll(mm));
+            mm &= mm - 1;
+            _Float16 hv[8];
+            const uint4 w = vmax[i >> 3];
+            __builtin_memcpy(hv, &w, sizeof(w));
+            if (float(hv[i & 7]) >= thrn) keep |= uint64_t(1) << i;
+          }
+          mask = keep;
+        }
+      }
+      // ---------------- angle of the best atom: the smallest angle index whose |score| is its
+      // maximum.  max(|E| + |O|) is bit for bit the largest rounded |E + O| or |E - O|, so the
+      // scores are compared with it for equality; rows past the valid angles score 0 and come
+      // last.  The rows ascend with the register in each half-wave: searched from the last.
+      int rs = 0x7fffffff;
+      float cval = 0.f;
+      if (SPLIT) {
+        const int HALF = R / 2;
+#pragma unroll
+        for (int h = 1; h >= 0; --h)
+#pragma unroll
+          for (int i = 15; i >= 0; --i) {
+            const float s = h == 0 ? E[0][i] + O[i] : E[0][i] - O[i];
+            const bool eq = fabsf(s) == best;
+            rs = eq ? 8 * (i / 4) + (i % 4) + 4 * u + h * HALF : rs;
+            cval = eq ? s : cval;
+          }
+      } else {
+#pragma unroll
+        for (int t = FT - 1; t >= 0; --t)
+#pragma unroll
+          for (int i = 15; i >= 0; --i) {
+            const float s = E[t][i];
+            const bool eq = fabsf(s) == best;
+            rs = eq ? 32 * t + 8 * (i / 4) + (i % 4) + 4 * u : rs;
+            cval = eq ? s : cval;
+          }
+      }
+      {
+        const float ov = __shfl_xor(cval, 32);
+        const int oc = __shfl_xor(rs, 32);
+        cval = oc < rs ? ov : cval;
+        rs = oc < rs ? oc : rs;
+        rs = rs < R ? rs : R - 1;
+      }
+      // ---------------- least squares
+      wave_lds_order();
+      StateIo<KMAX>::load(sState, col, st, ls);
+      n_sel += nc > 0 ? 1 : 0;
+      n_cand += nc;
+      max_cand = nc > max_cand ? nc : max_cand;
+      n_fp64 += ls_update<L, KMAX>(st, ls, it, bm, rs, cval, sHat, sCs, tb, p, u, res) ? 1 : 0;
+    }
+    const float rn2 = norm2<L>(res);
+    if (valid && u == 0) {
+#pragma unroll
+      for (int i = 0; i < KMAX; ++i) {
+        if (i < K) {
+          const bool s = i < st.nsel;
+          prm.atom[p * K + i] = s ? st.selm[i] : -1;
+          prm.angle[p * K + i] = s ? st.selr[i] : -1;
+          prm.coef[p * K + i] = s ? st.cf[i] : 0.f;
+        }
+      }
+      if (prm.resid2) prm.resid2[p] = rn2;
+    }
+  }
+  // per-wave totals of the counters (both half-waves counted), one atomic update per wave
+#pragma unroll
+  for (int off = 16; off >= 1; off >>= 1) {
+    n_sel += __shfl_xor(n_sel, off);
+    n_cand += __shfl_xor(n_cand, off);
+    n_fp64 += __shfl_xor(n_fp64, off);
+    const unsigned o = __shfl_xor(max_cand, off);
+    max_cand = o > max_cand ? o : max_cand;
+  }
+  if (lane == 0 && prm.stats) {
+    if (prm.count) {
+      atomicAdd(prm.stats + 0, (unsigned long long)n_sel);
+      atomicAdd(prm.stats + 1, (unsigned long long)n_cand);
+      atomicMax(prm.stats + 2, (unsigned long long)max_cand);
+    }
+    if (n_fp64) atomicAdd(prm.stats + 3, (unsigned long long)n_fp64);
+  }
+}
+
+// One launch: 8 waves per block where the tables and their states fit a CU's LDS, else 4.
+template <class C, int KMAX, int PREC, int RT, bool SPLIT>
+int launch(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
+  const int nw = screen_waves(t, KMAX);
+  if (nw == 0) return int(hipErrorInvalidValue);
+  const size_t lds = screen_lds_bytes(t, KMAX, nw);
+  auto kern = encode_screen_kernel<C, KMAX, PREC, RT, SPLIT>;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return int(e);
+  }
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * nw, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+  if (t.enc_bpc > 0) per_cu = max(1, min(per_cu, t.enc_bpc * 4 / nw));
+  const int64_t tiles = (prm.P + 31) / 32, cap = int64_t(num_cus()) * per_cu;
+  hipLaunchKernelGGL(kern, dim3(unsigned(tiles < cap ? tiles : cap)), dim3(64 * nw), lds, st, prm);
+  return int(hipGetLastError());
+}
+
+template <class C, int KMAX, int PREC>
+int launch_angles(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
+  if (t.R <= 32) return launch<C, KMAX, PREC, 1, false>(t, prm, st);
+  if (t.lpSplit) return launch<C, KMAX, PREC, 2, true>(t, prm, st);
+  return launch<C, KMAX, PREC, 2, false>(t, prm, st);
+}
+
+}  // namespace screen
+}  // namespace rsc

@@ -64,9 +64,10 @@ struct DeviceTables {
   float* dftA16s = nullptr;  // 16x16-tile stage-2 operand, parity split [ceil(R/32)->1,2,4][E+O steps][64]
   float* cs = nullptr;       // [2][T+1][R]: cos, then sin, of 2 pi k r / R
   float* gramH = nullptr;    // [M][M][2T+1]: per-atom-pair harmonic inner products (see pair_gram)
-  // 16-bit encoder (BF16 / FP16 handles)
-  uint16_t* lpA = nullptr;   // stage-1 operand [NG][T+1][64][8]
-  uint16_t* lpF16 = nullptr; // stage-2 operand [ceil(R/32)][64][8]
+  // screened encoder (rsc_screen.h): the screen's format (RSC_FP32: the sizes have no screen)
+  rsc_precision scrPrec = RSC_FP32;
+  uint16_t* lpA = nullptr;   // stage-1 operand [groups][steps][64][8]
+  uint16_t* lpF16 = nullptr; // stage-2 operand [operands][ceil(R/32)][64][8]
   float* lpF32 = nullptr;    // FP32 re-score angle DFT operand: [T+1][64] rows r < R/2 when
                              // lpSplit, else [ceil(R/32)][T+1][64]
   bool lpSplit = false;      // even R in 33..64: radix-2 split in the FP32 re-score
@@ -80,6 +81,20 @@ struct DeviceTables {
   int* lpPix16 = nullptr;
   float lpPinvUnscale = 1.f;  // 2^-s where the operand parts hold 2^s (Phi^T Phi)^{-1} Phi^T
 };
+
+// Arguments of the kernel that builds the dictionary tables from its rows (rsc_dict.hip); table
+// pointers as in DeviceTables, null where the handle has no such table.
+struct DictBuild {
+  const float* rows;   // device [M][B]
+  int M, B, T, nrows;  // nrows: rows of hat and hatI (16 ceil(M/16))
+  int sk[32], kbase[33];   // profiles of harmonic k, start of its block (kbase[T + 1] = B)
+  bool bf16;           // the screen's format (else FP16)
+  float *hat, *hatI, *dictA;
+  uint16_t* lpA;
+  float* gramH;
+  double* gramH64;
+};
+int launch_dict_tables(const DictBuild& p, void* stream);
 
 // Kernel launchers.  Return a hipError_t as int.
 int launch_project(const DeviceTables& t, const float* patches, int64_t P, float* xhat, void* stream);
@@ -138,11 +153,15 @@ int launch_chi2_nearest(const float* train, int n_train, const float* test, int 
 constexpr int kSumBlocks = 256;
 constexpr int kSumSlots = kSumBlocks + 1;
 int launch_sum(const float* x, int64_t n, double* out, void* stream);
-bool encode_lp_supported(int S, int T, int M, int R);
-size_t encode_lp_lds_bytes(const DeviceTables& t);
-double encode_lp_mfma_flops_per_patch(const DeviceTables& t, int K);
-int launch_encode_lp(const DeviceTables& t, int prec, const float* xhat, int64_t P, int K, int32_t* atom,
-                     int32_t* angle, float* coef, float* resid2, void* stream);
+// Screened encoder (rsc_encode_screen.h): whether a layout, M and R have one, whether it fits
+// the LDS for K, its block's LDS and waves, its 16-bit MFMA work, and the launch.
+bool screen_supported(int geo, int S, int T, int M, int R);
+bool screen_usable(const DeviceTables& t, int K);
+size_t screen_lds_bytes(const DeviceTables& t, int kmax, int waves);
+int screen_waves(const DeviceTables& t, int kmax);
+double screen_mfma_flops_per_patch(const DeviceTables& t, int K);
+int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
+                         float* coef, float* resid2, void* stream);
 size_t images_workspace_bytes(int n_images);
 // rsc_project_images_noalloc: the plan in a static device array of this many images.
 constexpr int kNoAllocMaxImages = 65535;
