@@ -222,6 +222,19 @@ float from_f16(uint16_t b) {
   return float(h);
 }
 
+// The handle's pair table (d.sk set): per harmonic-0 coordinate and per profile of harmonic k >= 1
+// its Re and Im coordinate and k.
+rsc_status upload_pairs(rsc::DeviceTables& d) {
+  std::vector<int> tab;
+  int base = 0;
+  for (int k = 0; k <= d.T; ++k) {
+    const int nk = d.sk[k];
+    for (int s = 0; s < nk; ++s) tab.push_back((base + s) | (base + (k == 0 ? 0 : nk) + s) << 8 | k << 16);
+    base += k == 0 ? nk : 2 * nk;
+  }
+  return upload(d.pairTab, tab, "pair table");
+}
+
 // Device tables of a handle whose host basis is built (shared by every kind of handle).
 // On failure the handle is destroyed.
 rsc_status init_tables(rsc_handle* h, int N, int S, int T, rsc_precision prec) {
@@ -411,6 +424,11 @@ rsc_status rsc_create(int N, int S, int T, const double* centres, double sigma, 
   }
   rsc_status st = init_tables(h, N, S, T, prec);
   if (st != RSC_OK) return st;
+  st = upload_pairs(h->dev);
+  if (st != RSC_OK) {
+    rsc_destroy(h);
+    return st;
+  }
   *out = h;
   return ok();
 }
@@ -445,6 +463,11 @@ rsc_status rsc_create_annular(int N, int lowpass, rsc_handle** out) {
   h->dev.geo = (N == 11 && !lowpass && h->Ts == ts11)   ? rsc::kGeoAnnular11
                : (N == 15 && !lowpass && h->Ts == ts15) ? rsc::kGeoAnnular15
                                                         : rsc::kGeoAnnularOther;
+  st = upload_pairs(h->dev);
+  if (st != RSC_OK) {
+    rsc_destroy(h);
+    return st;
+  }
   // steering table: coordinate -> (harmonic k, offset of its Re/Im partner)
   std::vector<int> tab(b.B);
   int col = 0;
@@ -512,6 +535,7 @@ rsc_status rsc_destroy(rsc_handle* h) {
   free_dev(d.phiPad);
   free_dev(d.synA);
   free_dev(d.steerTab);
+  free_dev(d.pairTab);
   release_slot(h->slot[0]);
   release_slot(h->slot[1]);
   d.dictArena = nullptr;
@@ -934,7 +958,7 @@ rsc_status rsc_reconstruct(const rsc_handle* h, const int32_t* atom, const int32
   if (P > (int64_t(1) << 31) * 8) return fail(RSC_E_INVALID, "P too large");
   if (rsc_status f = check_fault(h)) return f;
   return dict_launch(h, stream, "reconstruct launch", [&] {
-    return rsc::launch_synthesize(h->dev, atom, angle, nullptr, coef, P, K, nullptr, out, stream);
+    return rsc::launch_reconstruct(h->dev, atom, angle, coef, P, K, out, stream);
   });
 }
 

@@ -49,6 +49,7 @@ struct DeviceTables {
   int* dpixI = nullptr;      // (dy << 8 | dx) of disk pixel i, -1 past n_pix [2*ceil(n_pix/2)]
   int* steerTab = nullptr;   // annular basis: per coordinate, harmonic k and partner offset
                              // ((k << 16) | (offset + 32768)); null for the full (S, T) grid
+  int* pairTab = nullptr;    // (Re, Im) pairs and harmonic-0 coordinates: Re index | Im index << 8 | harmonic << 16
   float* phiPad = nullptr;   // synthesis matrix [N*N][B]
   float* synA = nullptr;     // synthesis MFMA operand [ceil(N*N/32)][ceil(B/2)][64] (N*N <= 256)
   // Dictionary tables (dictA .. cs64 below) point into the bound one of the handle's two
@@ -103,6 +104,8 @@ int launch_encode(const DeviceTables& t, int tile, const float* xhat, int64_t P,
 int launch_synthesize(const DeviceTables& t, const int32_t* atom, const int32_t* angle_idx,
                       const float* theta, const float* weight, int64_t P, int J,
                       const float* noise, float* out, void* stream);
+int launch_reconstruct(const DeviceTables& t, const int32_t* atom, const int32_t* angle, const float* coef, int64_t P,
+                       int K, float* out, void* stream);
 bool encode_supported(int S, int T);
 bool encode_supported_geo(const DeviceTables& t);   // the encoder is compiled for t's layout
 // The pursuit on the paper's annular basis (rsc_encode_annular.hip): 16x16 tiles, even
