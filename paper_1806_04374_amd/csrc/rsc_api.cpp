@@ -717,10 +717,12 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
   const size_t staged = arena.staging.size(), nhat = size_t(NG) * 16 * B, ngram = size_t(M) * M * HQ;
   arena.reserve(nd.dictHat, nhat);
   arena.reserve(nd.dictHatI, lp ? 0 : nhat);
+  arena.reserve(nd.dictPairs, screened ? size_t(NG) * 16 * rsc::screen_row(B, d.sk[0]) : 0);
   arena.reserve(nd.dictA, S == 5 && T == 5 ? size_t(NG) * rsc::stage1_steps(S, T) * 64 : 0);
   arena.reserve(nd.lpA, nlpA);
   arena.reserve(nd.gramH, ngram);
   arena.reserve(nd.gramH64, ngram);
+  arena.reserve(nd.norm2, M);
   const size_t need = arena.total;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   DictSlot& sl = h->slot[h->cur < 0 ? 0 : 1 - h->cur];
@@ -760,8 +762,8 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
   if ((e = hipMemcpyAsync(sl.arena, sl.pinned, staged, hipMemcpyHostToDevice, st)) != hipSuccess)
     return handle_fail(h, int(e), "dictionary upload");
   arena.bind(static_cast<char*>(sl.arena));
-  rsc::DictBuild build{rows, M, B, T, NG * 16, {}, {}, scr == RSC_BF16, nd.dictHat, nd.dictHatI, nd.dictA, nd.lpA,
-                       nd.gramH, nd.gramH64};
+  rsc::DictBuild build{rows, M, B, T, NG * 16, {}, {}, scr == RSC_BF16, nd.dictHat, nd.dictHatI, nd.dictPairs,
+                       nd.dictA, nd.lpA, nd.gramH, nd.norm2, nd.gramH64};
   for (int k = 0; k <= T; ++k) {
     build.sk[k] = d.sk[k];
     build.kbase[k + 1] = build.kbase[k] + (k == 0 ? 1 : 2) * d.sk[k];

@@ -227,11 +227,22 @@ __device__ __forceinline__ void atom_operand(const float* __restrict__ hat, int 
   }
 }
 
+// x of the other half-wave's lane (lane ^ 32): one lane swap instead of a trip through the LDS
+// crossbar, whose latency sits on every step's serial chain.
+__device__ __forceinline__ unsigned other_half(unsigned x, int u) {
+  auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);   // [lo | lo], [hi | hi]
+  return u ? r[0] : r[1];
+}
+__device__ __forceinline__ float other_half(float x, int u) { return __uint_as_float(other_half(__float_as_uint(x), u)); }
+__device__ __forceinline__ int other_half(int x, int u) { return int(other_half(unsigned(x), u)); }
+
 // Sum over the W lanes of a patch; bit-identical in all of them.
 template <int W>
 __device__ __forceinline__ float patch_sum(float x) {
-  if (W == 4) x = x + __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
+  if (W == 4) return (x = x + __shfl_xor(x, 16)) + __shfl_xor(x, 32);
+  float a = x, b = x;
+  swap32(a, b);                                                    // [lo | lo], [hi | hi]
+  return a + b;
 }
 
 // acc += alpha * S_r d_m on the coordinates sub-lane u holds (steering computed on

@@ -51,6 +51,22 @@ __global__ __launch_bounds__(256) void dict_tables_kernel(DictBuild p) {
       p.gramH[o + 2 * k] = float(im);
     }
   }
+  // squared norms: the harmonics' own products, rounded and then added in FP32, which is what the
+  // pair table gives an atom with itself
+  for (int64_t m = i0; m < M; m += stride) {
+    float n2 = 0.f;
+    for (int k = 0; k <= T; ++k) {
+      double h = 0.0;
+      const float* r = p.rows + size_t(m) * B + p.kbase[k];
+      const int nk = p.sk[k];
+      for (int s = 0; s < nk; ++s) {
+        const double a = r[s], b = k ? r[nk + s] : 0.0;
+        h += a * a + b * b;
+      }
+      n2 = n2 + float(h);
+    }
+    p.norm2[m] = n2;
+  }
   // rows padded with zero atoms, and i times them: per harmonic k >= 1 the (Re, Im) slots hold
   // (-Im d, Re d), zero at harmonic 0
   for (int64_t i = i0; i < int64_t(p.nrows) * B; i += stride) {
@@ -61,6 +77,24 @@ __global__ __launch_bounds__(256) void dict_tables_kernel(DictBuild p) {
       while (k < T && c >= p.kbase[k + 1]) ++k;
       const int nk = p.sk[k];
       p.hatI[i] = k == 0 ? 0.f : c - p.kbase[k] < nk ? -D(m, c + nk) : D(m, c - nk);
+    }
+  }
+  // rows of the screened encoder: harmonic 0 padded to an even count, then (Re, Im) pairs
+  if (p.pairs) {
+    const int row = screen_row(B, p.sk[0]), s0 = p.sk[0] + p.sk[0] % 2;
+    for (int64_t i = i0; i < int64_t(p.nrows) * row; i += stride) {
+      const int m = int(i / row), e = int(i - int64_t(m) * row);
+      float v = 0.f;
+      if (e < s0) {
+        if (e < p.sk[0]) v = D(m, e);
+      } else if (e - s0 + p.sk[0] < B) {
+        const int c = e - s0 + p.sk[0];        // the packed coordinate at this place
+        int k = 1;
+        while (k < T && c >= p.kbase[k + 1]) ++k;
+        const int rem = c - p.kbase[k];
+        v = D(m, p.kbase[k] + (rem % 2) * p.sk[k] + rem / 2);
+      }
+      p.pairs[i] = v;
     }
   }
   // 32x32 FP32 tiles, stage-1 operand: row 8i + j (j < 4) gives Re C_k of atom 16g + 4i + j and

@@ -29,7 +29,7 @@
 //     maxima are kept for this as FP16 fractions of ||r|| in private memory, which is read only
 //     for candidates, with a margin of 2^-10 for their rounding.  FP16's window holds about one
 //     atom, and the bookkeeping would cost more than it saves.
-//   least squares and residual update in FP32 (ls_update), as in the FP32 encoders.
+//   least squares and residual update in FP32 (ls_step), as in the FP32 encoders.
 //
 // What bounds it: vector issue.  A wave's maxima over 64 angles cost 16 three-way maxima per
 // atom for 32 patches, and the 16-bit products take as many cycles on the matrix cores, so
@@ -53,11 +53,13 @@ struct ScreenParams {
   int64_t P;
   int K, M, R;
   const uint4* dictA;      // stage-1 operand [NG][NJ][64] x 8 16-bit values
-  const float* dictHat;    // [>= NG AG][B]
+  const float* pairs;      // [>= NG AG][screen_row] dictionary rows (rsc_screen.h)
+  const float* dictHat;    // [>= M][B] (the FP64 re-solve)
   const uint4* dft16;      // stage-2 operand [OPS][RT][64] x 8 16-bit values
   const float* dft32;      // FP32 angle DFT [FT][NQ][64]
   const float* cs;         // [2][NQ][R]
   const float* gramH;      // [M][M][2T+1]
+  const float* norm2;      // [M] squared norms of the atoms
   const double* gramH64;   // [M][M][2T+1]
   const double* cs64;      // [2][NQ][R]
   int32_t* atom;
@@ -70,10 +72,10 @@ struct ScreenParams {
 };
 
 // The least-squares state of the wave's 32 patches in LDS: float4 q of patch col at
-// st[q * 32 + col].  Both half-waves hold the same values; the low one writes.
+// mem[q * 32 + col].  Both half-waves hold the same values; the low one writes.
 template <int KMAX>
 struct StateIo {
-  static constexpr int N4 = screen_state_f4(KMAX);
+  static constexpr int N4 = screen_state_f4(KMAX), NF = KMAX * (KMAX - 1) / 2 + 3 * KMAX;
   template <class F>
   __device__ __forceinline__ static void each(PursuitState<KMAX>& st, LsState<KMAX>& ls, F f) {
     int n = 0;
@@ -92,6 +94,14 @@ struct StateIo {
     float v[4 * N4];
     zero(v);
     each(st, ls, [&](int n, float& x) { v[n] = x; });
+    // selections as 16-bit words: atom << 6 | angle (M <= 128, R <= 64), -1 for an empty slot
+#pragma unroll
+    for (int i = 0; i < KMAX; i += 2) {
+      const int a = st.selm[i] < 0 ? -1 : st.selm[i] << 6 | st.selr[i];
+      const int b = i + 1 >= KMAX || st.selm[i + 1 < KMAX ? i + 1 : i] < 0
+                        ? -1 : st.selm[i + 1 < KMAX ? i + 1 : i] << 6 | st.selr[i + 1 < KMAX ? i + 1 : i];
+      v[NF + i / 2] = __int_as_float((a & 0xffff) | b << 16);
+    }
     if (lane < 32) {
 #pragma unroll
       for (int q = 0; q < N4; ++q) mem[q * 32 + lane] = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
@@ -108,8 +118,252 @@ struct StateIo {
       v[4 * q + 3] = w.w;
     }
     each(st, ls, [&](int n, float& x) { x = v[n]; });
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) {
+      const int w = __float_as_int(v[NF + i / 2]), z = i % 2 ? w >> 16 : w << 16 >> 16;
+      st.selm[i] = z >> 6;
+      st.selr[i] = z < 0 ? -1 : z & 63;
+    }
   }
 };
+
+// Orders the low half-wave's LDS writes before the whole wave's reads: neither the compiler (which
+// sees a conditional store and a load of one thread) nor the hardware moves one past the other.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// A dictionary row (rsc_screen.h) goes through registers in batches of whole harmonics of up to
+// kRowPairs pairs, the next batch's LDS reads issued before the current one is used.  Left to
+// itself the compiler waits for every read or two, and the reads' latency, not their number,
+// was most of a step outside the screen.
+constexpr int kRowPairs = 16;
+template <class L>
+struct RowBatches {
+  __host__ __device__ static constexpr int next(int k) {     // first harmonic of the batch after k's
+    int n = L::Sk(k), q = k + 1;
+    while (q <= L::T && n + L::Sk(q) <= kRowPairs) n += L::Sk(q++);
+    return q;
+  }
+  __host__ __device__ static constexpr int first(int b) {    // first harmonic of batch b
+    int k = 1;
+    for (int i = 0; i < b && k <= L::T; ++i) k = next(k);
+    return k;
+  }
+  __host__ __device__ static constexpr int count() {
+    int b = 0;
+    for (int k = 1; k <= L::T; k = next(k)) ++b;
+    return b;
+  }
+  // index of harmonic k's first pair within the row's pairs, and the floats before the pairs
+  __host__ __device__ static constexpr int pair0(int k) { return (L::base(k) - L::Sk(0)) / 2; }
+  static constexpr int S0 = 2 * L::J0;
+  // f(k, i, (Re, Im)) for every profile i of every harmonic k >= 1, g(k) after each harmonic
+  template <class F, class G>
+  __device__ __forceinline__ static void each(const float* __restrict__ row, F f, G g) {
+    const float2* pr = reinterpret_cast<const float2*>(row + S0);
+    float2 buf[2][kRowPairs];
+    auto fetch = [&](auto B1) {
+      constexpr int b = decltype(B1)::value, lo = pair0(first(b)), hi = pair0(first(b + 1) <= L::T ? first(b + 1) : L::T + 1);
+#pragma unroll
+      for (int i = lo; i < hi; ++i) buf[b % 2][i - lo] = pr[i];
+    };
+    fetch(std::integral_constant<int, 0>{});
+    static_for<count()>([&](auto B1) {
+      constexpr int b = decltype(B1)::value, k0 = first(b), k1 = b + 1 < count() ? first(b + 1) : L::T + 1;
+      if constexpr (b + 1 < count()) fetch(std::integral_constant<int, b + 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<k1 - k0>([&](auto K1) {
+        constexpr int k = k0 + decltype(K1)::value;
+        static_for<L::Sk(k)>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          f(std::integral_constant<int, k>{}, std::integral_constant<int, i>{}, buf[b % 2][pair0(k) - pair0(k0) + i]);
+        });
+        g(std::integral_constant<int, k>{});
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+};
+
+// C_k = sum_s conj(d_{m,s,k}) x_{s,k} of the atom in `row` for this lane's patch: op[k] = Re C_k in
+// the low half-wave and Im C_k in the high one (atom_operand, on a row of pairs).  Each half-wave
+// multiplies its residual coordinates (Re parts low, Im parts high) with both parts of the
+// atom, and one swap per harmonic adds the halves' sums.
+template <class L>
+__device__ __forceinline__ void row_operand(const float* __restrict__ row, int u, const float (&res)[L::NKS],
+                                            float (&op)[L::NQ]) {
+  float d0[L::J0];
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) d0[j] = row[2 * j + u];
+  float pr[L::NQ], pi[L::NQ];
+  zero(pr);
+  zero(pi);
+  RowBatches<L>::each(row, [&](auto K1, auto I, float2 d) {
+    constexpr int k = decltype(K1)::value, j = L::joff(k) + decltype(I)::value;
+    pr[k] = fmaf(d.x, res[j], pr[k]);
+    pi[k] = fmaf(d.y, res[j], pi[k]);
+  }, [&](auto K1) {
+    // low (Re x): Re += dRe x, Im -= dIm x; high (Im x): Re += dIm x, Im += dRe x
+    constexpr int k = decltype(K1)::value;
+    float x = u ? pi[k] : pr[k], y = u ? pr[k] : -pi[k];
+    swap32(x, y);
+    op[k] = x + y;
+  });
+  float p0 = 0.f;
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) p0 = fmaf(d0[j], res[j], p0);
+  float x = p0, y = 0.f;
+  swap32(x, y);
+  op[0] = x + y;
+}
+
+// acc += alpha S_r d for the atom in `row` on this lane's coordinates; cs: (cos, sin) of this
+// angle per harmonic.  Re' = c Re + s Im, Im' = c Im - s Re: the two factors of a harmonic's
+// (Re, Im) pair are picked per lane once, so a coordinate costs two fused multiply-adds.
+template <class L>
+__device__ __forceinline__ void row_axpy(float (&acc)[L::NKS], float alpha, const float* __restrict__ row,
+                                         const float2* __restrict__ cs, int u) {
+  float d0[L::J0];
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) d0[j] = row[2 * j + u];
+  float2 w[L::NQ];
+#pragma unroll
+  for (int k = 1; k < L::NQ; ++k) w[k] = cs[k];
+  float fx = 0.f, fy = 0.f;
+  RowBatches<L>::each(row, [&](auto K1, auto I, float2 d) {
+    constexpr int k = decltype(K1)::value, i = decltype(I)::value, j = L::joff(k) + i;
+    if constexpr (i == 0) {
+      const float c = alpha * w[k].x, s = alpha * w[k].y;
+      fx = u ? -s : c;
+      fy = u ? c : s;
+    }
+    acc[j] = fmaf(d.x, fx, fmaf(d.y, fy, acc[j]));
+  }, [](auto) {});
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) acc[j] = fmaf(alpha, d0[j], acc[j]);
+}
+
+// The least-squares step of ls_update (same formulas and thresholds) with what it indexes by
+// slot at run time kept in the wave's LDS, `mem`: one copy of the code steers every selected
+// column, instead of one per slot, and the half-waves share the pair products (slot 2i + u).
+template <class L, int KMAX>
+__device__ __forceinline__ bool ls_step(PursuitState<KMAX>& st, LsState<KMAX>& ls, int it, int ms, int rs, float cval,
+                                        const float* pairs, int row, const float2* cs, const LsTables& tb,
+                                        const float* norm2, const float* hat, int64_t p, int u, int col, float* mem,
+                                        float (&res)[L::NKS]) {
+  constexpr int T = L::T, HQ = 2 * T + 1, AS = screen_angle_stride(T);
+  const int M = tb.M, R = tb.R;
+  const float dd = norm2[ms];
+  int* sel = reinterpret_cast<int*>(mem) + col;      // [KMAX] x 32: atom << 6 | angle of slot i
+  float* val = mem + KMAX * 32 + col;                // [KMAX] x 32: pair product, then coefficient change
+  bool dup = false;
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    dup = dup || (i < it && st.selm[i] == ms && st.selr[i] == rs);
+    const int z = st.selm[i] < 0 ? 0 : st.selm[i] << 6 | st.selr[i];
+    if (u == 0) sel[i * 32] = i == it ? ms << 6 | rs : z;
+  }
+  const bool upd = st.active && !dup;
+  wave_lds_order();
+  // <column i, new column> for i < it
+  for (int i0 = 0; i0 < it; i0 += 2) {
+    const int i = i0 + u < it ? i0 + u : i0;
+    const int z = sel[i * 32], a = z >> 6;
+    int dr = (z & 63) - rs;
+    dr += dr < 0 ? R : 0;
+    const float* h = tb.gramH + (size_t(a) * M + ms) * HQ;
+    float hv[HQ];
+#pragma unroll
+    for (int k = 0; k < HQ; ++k) hv[k] = h[k];
+    const float2* w = cs + dr * AS;
+    float g = hv[0];
+#pragma unroll
+    for (int k = 1; k <= T; ++k) g += w[k].x * hv[2 * k - 1] - w[k].y * hv[2 * k];
+    val[i * 32] = g;
+  }
+  wave_lds_order();
+  float gcol[KMAX];
+  float bx = cval;
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    gcol[i] = i < it ? val[i * 32] : 0.f;
+    bx += gcol[i] * st.cf[i];
+  }
+  float w[KMAX];
+  float l2 = dd;
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    float s = gcol[i];
+#pragma unroll
+    for (int j = 0; j < i; ++j) s -= st.L[i][j] * w[j];
+    w[i] = i < it ? s * ls.Ld[i] : 0.f;
+    l2 -= w[i] * w[i];
+  }
+  // new row of L^{-1}: [-(L^{-T} w)^T, 1] / l, so ||L^{-1}||_F^2 grows by (|L^{-T} w|^2 + 1) / l^2
+  float z[KMAX];
+  float zz = 0.f;
+#pragma unroll
+  for (int i = KMAX - 1; i >= 0; --i) {
+    float s = w[i];
+#pragma unroll
+    for (int j = i + 1; j < KMAX; ++j) s -= (j < it ? st.L[j][i] : 0.f) * z[j];
+    z[i] = i < it ? s * ls.Ld[i] : 0.f;
+    zz += z[i] * z[i];
+  }
+  const float Fn = ls.condF + (zz + 1.f) / fmaxf(l2, 1e-30f);
+  const bool ok32 = !ls.fp64 && l2 > 1e-6f * dd && float(it + 1) * Fn <= tb.cond_max;
+  const bool up32 = upd && ok32;
+  const bool go64 = upd && !ok32;
+#pragma unroll
+  for (int r = 0; r < KMAX; ++r) {
+    const bool here = up32 && r == it;
+#pragma unroll
+    for (int i = 0; i < r; ++i) st.L[r][i] = here ? w[i] : st.L[r][i];
+    ls.Ld[r] = here ? rsqrtf(l2) : ls.Ld[r];
+    st.bv[r] = here ? bx : st.bv[r];
+    st.selm[r] = here ? ms : st.selm[r];
+    st.selr[r] = here ? rs : st.selr[r];
+  }
+  float y[KMAX], an[KMAX];
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) {
+    float s = st.bv[i];
+#pragma unroll
+    for (int j = 0; j < i; ++j) s -= st.L[i][j] * y[j];
+    y[i] = i <= it ? s * ls.Ld[i] : 0.f;
+  }
+#pragma unroll
+  for (int i = KMAX - 1; i >= 0; --i) {
+    float s = y[i];
+#pragma unroll
+    for (int j = i + 1; j < KMAX; ++j) s -= st.L[j][i] * an[j];
+    an[i] = i <= it ? s * ls.Ld[i] : 0.f;
+  }
+  if (__any(up32)) {
+    wave_lds_order();                                // the pair products have been read
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i)
+      if (u == 0) val[i * 32] = up32 && i <= it ? st.cf[i] - an[i] : 0.f;
+    wave_lds_order();
+#pragma unroll 1
+    for (int i = 0; i <= it; ++i) {
+      const int zi = sel[i * 32];
+      row_axpy<L>(res, val[i * 32], pairs + (zi >> 6) * row, cs + (zi & 63) * AS, u);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < KMAX; ++i) st.cf[i] = (up32 && i <= it) ? an[i] : st.cf[i];
+  ls.condF = up32 ? Fn : ls.condF;
+  bool ok64 = false;
+  if (__any(go64)) ok64 = ls_solve64<L, KMAX>(st, it, ms, rs, go64, hat, tb, p, u, res);
+  ls.fp64 = ls.fp64 || ok64;
+  st.nsel = (up32 || ok64) ? it + 1 : st.nsel;
+  st.active = up32 || ok64;
+  return go64;
+}
 
 // A patch's coordinates x [B] into the registers of its two lanes (W = 2): register j of
 // harmonic k >= 1 reads the Re part in the low half-wave and the Im part, Sk(k) further on, in
@@ -131,17 +385,9 @@ __device__ __forceinline__ void load_hat(const float* __restrict__ x, int u, boo
   for (int j = 0; j < L::NKS; ++j) res[j] = valid ? res[j] : 0.f;
 }
 
-// Orders the low half-wave's LDS writes before the whole wave's reads: neither the compiler (which
-// sees a conditional store and a load of one thread) nor the hardware moves one past the other.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // Bytes of the tables that a block keeps in LDS, rounded up to 16.
-__host__ __device__ constexpr size_t screen_table_bytes(int NG, int NJ, int NQ, int rows, int B, int R, int FT) {
-  return size_t(NG) * NJ * 1024 + ((sizeof(float) * (size_t(rows) * B + 2 * size_t(NQ) * R + size_t(FT) * NQ * 64) + 15) & ~size_t(15));
+__host__ __device__ constexpr size_t screen_table_bytes(int NG, int NJ, int NQ, int rows, int row, int R, int FT) {
+  return size_t(NG) * NJ * 1024 + ((sizeof(float) * (size_t(rows) * row + 2 * size_t(NQ | 1) * R + size_t(FT) * NQ * 64) + 15) & ~size_t(15));
 }
 
 // RT: 32-angle tiles of the screen (ceil(R / 32)).  SPLIT: the FP32 scores use the radix-2
@@ -159,17 +405,21 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
   extern __shared__ uint4 lds4[];
   const int R = prm.R, M = prm.M, K = prm.K, NG = (M + AG - 1) / AG, rows = NG * AG;
   const V8* sA = reinterpret_cast<const V8*>(lds4);             // [NG][NJ][64]
-  float* sHat = reinterpret_cast<float*>(lds4 + NG * NJ * 64);  // [rows][B]
-  float* sCs = sHat + rows * B;                                 // [2][NQ][R]
-  float* sF = sCs + 2 * NQ * R;                                 // [FT][NQ][64]
+  constexpr int RB = screen_row(B, L::Sk(0)), AS = screen_angle_stride(T);
+  float* sHat = reinterpret_cast<float*>(lds4 + NG * NJ * 64);  // [rows][RB]
+  float2* sCs = reinterpret_cast<float2*>(sHat + rows * RB);    // [R][AS] (cos, sin)
+  float* sF = reinterpret_cast<float*>(sCs + AS * R);           // [FT][NQ][64]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = int(blockDim.x) >> 6;
-  float4* sState = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds4) + screen_table_bytes(NG, NJ, NQ, rows, B, R, FT)) +
+  float4* sState = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds4) + screen_table_bytes(NG, NJ, NQ, rows, RB, R, FT)) +
                    wave * (StateIo<KMAX>::N4 * 32);
   {
-    const int nA = NG * NJ * 64, nH = rows * B, nC = 2 * NQ * R, nF = FT * NQ * 64;
+    const int nA = NG * NJ * 64, nH = rows * RB, nC = NQ * R, nF = FT * NQ * 64;
     for (int i = threadIdx.x; i < nA; i += blockDim.x) lds4[i] = prm.dictA[i];
-    for (int i = threadIdx.x; i < nH; i += blockDim.x) sHat[i] = prm.dictHat[i];
-    for (int i = threadIdx.x; i < nC; i += blockDim.x) sCs[i] = prm.cs[i];
+    for (int i = threadIdx.x; i < nH; i += blockDim.x) sHat[i] = prm.pairs[i];
+    for (int i = threadIdx.x; i < nC; i += blockDim.x) {
+      const int r = i / NQ, k = i - r * NQ;
+      sCs[r * AS + k] = float2{prm.cs[k * R + r], prm.cs[(NQ + k) * R + r]};
+    }
     for (int i = threadIdx.x; i < nF; i += blockDim.x) sF[i] = prm.dft32[i];
   }
   __syncthreads();
@@ -324,11 +574,11 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         }
         vh = nvh;
       }
-      const float vo = __shfl_xor(vh, 32);
+      const float vo = other_half(vh, u);
       if (!(vh >= fmaxf(vh, vo) - wnd) || !st.active) mask = 0;
       // with the filter: the atom of the largest 16-bit maximum (the low half-wave's on equal
       // maxima) goes first
-      const int vao = kFilter ? __shfl_xor(va, 32) : 0;
+      const int vao = kFilter ? other_half(va, u) : 0;
       const int m1 = (u == 0 ? vh >= vo : vo < vh) ? va : vao;
       const bool has1 = st.active && fmaxf(vh, vo) >= 0.f;
       if (kFilter && has1 && (m1 & 1) == u) mask &= ~(uint64_t(1) << (m1 >> 1));
@@ -352,7 +602,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
           has = has1;
         } else {
           const int mine = mask ? 2 * int(__builtin_ctzll(mask)) + u : 0x7fffffff;
-          m = min(mine, __shfl_xor(mine, 32));
+          m = min(mine, other_half(mine, u));
           has = m != 0x7fffffff;
           if (has && mine == m) mask &= mask - 1;
         }
@@ -360,7 +610,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         nc += has ? 1 : 0;
         const int mc = has ? m : 0;
         float op32[NQ];
-        atom_operand<L>(sHat, mc, u, res, op32);
+        row_operand<L>(sHat + mc * RB, u, res, op32);
         f32x16 e[FT], o;
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i] = 0.f;
@@ -433,8 +683,8 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
           }
       }
       {
-        const float ov = __shfl_xor(cval, 32);
-        const int oc = __shfl_xor(rs, 32);
+        const float ov = other_half(cval, u);
+        const int oc = other_half(rs, u);
         cval = oc < rs ? ov : cval;
         rs = oc < rs ? oc : rs;
         rs = rs < R ? rs : R - 1;
@@ -442,10 +692,12 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       // ---------------- least squares
       wave_lds_order();
       StateIo<KMAX>::load(sState, col, st, ls);
+      wave_lds_order();
       n_sel += nc > 0 ? 1 : 0;
       n_cand += nc;
       max_cand = nc > max_cand ? nc : max_cand;
-      n_fp64 += ls_update<L, KMAX>(st, ls, it, bm, rs, cval, sHat, sCs, tb, p, u, res) ? 1 : 0;
+      n_fp64 += ls_step<L, KMAX>(st, ls, it, bm, rs, cval, sHat, RB, sCs, tb, prm.norm2, prm.dictHat, p, u, col,
+                                 reinterpret_cast<float*>(sState), res) ? 1 : 0;
     }
     const float rn2 = norm2<L>(res);
     if (valid && u == 0) {
@@ -461,7 +713,9 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       if (prm.resid2) prm.resid2[p] = rn2;
     }
   }
-  // per-wave totals of the counters (both half-waves counted), one atomic update per wave
+  // totals of the counters: over the wave (both half-waves hold them), then over the block in
+  // LDS, then one set of atomics per block (one per wave, 2,048 on one line, kept the memory
+  // system busy past the work of a small launch)
 #pragma unroll
   for (int off = 16; off >= 1; off >>= 1) {
     n_sel += __shfl_xor(n_sel, off);
@@ -470,13 +724,24 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
     const unsigned o = __shfl_xor(max_cand, off);
     max_cand = o > max_cand ? o : max_cand;
   }
-  if (lane == 0 && prm.stats) {
-    if (prm.count) {
-      atomicAdd(prm.stats + 0, (unsigned long long)n_sel);
-      atomicAdd(prm.stats + 1, (unsigned long long)n_cand);
-      atomicMax(prm.stats + 2, (unsigned long long)max_cand);
+  __syncthreads();                                   // the tables are no longer read
+  unsigned* tot = reinterpret_cast<unsigned*>(lds4);
+  if (threadIdx.x < 4) tot[threadIdx.x] = 0u;
+  __syncthreads();
+  if (lane == 0 && n_sel + n_fp64 > 0) {
+    atomicAdd(tot + 0, n_sel);
+    atomicAdd(tot + 1, n_cand);
+    atomicMax(tot + 2, max_cand);
+    atomicAdd(tot + 3, n_fp64);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && prm.stats) {
+    if (prm.count && tot[0]) {
+      atomicAdd(prm.stats + 0, (unsigned long long)tot[0]);
+      atomicAdd(prm.stats + 1, (unsigned long long)tot[1]);
+      atomicMax(prm.stats + 2, (unsigned long long)tot[2]);
     }
-    if (n_fp64) atomicAdd(prm.stats + 3, (unsigned long long)n_fp64);
+    if (tot[3]) atomicAdd(prm.stats + 3, (unsigned long long)tot[3]);
   }
 }
 

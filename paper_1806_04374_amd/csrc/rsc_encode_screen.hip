@@ -19,7 +19,7 @@ int kmax_of(const DeviceTables& t, int K) {
 size_t table_bytes(const DeviceTables& t) {
   const int ag = screen_group_atoms(t.T), ng = (t.M + ag - 1) / ag;
   const int ft = t.R <= 32 || t.lpSplit ? 1 : 2;
-  return screen::screen_table_bytes(ng, screen_steps(t.T), t.T + 1, ng * ag, t.B, t.R, ft);
+  return screen::screen_table_bytes(ng, screen_steps(t.T), t.T + 1, ng * ag, screen_row(t.B, t.sk[0]), t.R, ft);
 }
 
 }  // namespace
@@ -54,8 +54,8 @@ int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, in
                          float* coef, float* resid2, void* stream) {
   if (P <= 0) return 0;
   const screen::ScreenParams prm{xhat, P, K, t.M, t.R,
-                                 reinterpret_cast<const uint4*>(t.lpA), t.dictHat,
-                                 reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.gramH64, t.cs64,
+                                 reinterpret_cast<const uint4*>(t.lpA), t.dictPairs, t.dictHat,
+                                 reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.norm2, t.gramH64, t.cs64,
                                  atom, angle, coef, resid2, t.lpStats,
                                  t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32};
   if (t.geo == kGeoAnnular11) {

@@ -60,11 +60,13 @@ struct DeviceTables {
   float* dictHat = nullptr;  // dictionary rows [16*ceil(M/16)][B] (zero rows past M)
   float* dictHatI = nullptr; // i times the dictionary rows, same shape: per harmonic k >= 1 the
                              // (Re, Im) slots hold (-Im d, Re d); zero at k = 0 (16x16 FP32 tile)
+  float* dictPairs = nullptr;  // rows of the screened encoder (rsc_screen.h) [16*ceil(M/16)][screen_row]
   float* dftA32 = nullptr;   // 32x32-tile stage-2 operand, angles r < R/2 [T+1][64] (even R <= 64)
   float* dftA16 = nullptr;   // 16x16-tile stage-2 operand, all angles [ceil(R/16)->1,2,4,8][(T+2)/2][64]
   float* dftA16s = nullptr;  // 16x16-tile stage-2 operand, parity split [ceil(R/32)->1,2,4][E+O steps][64]
   float* cs = nullptr;       // [2][T+1][R]: cos, then sin, of 2 pi k r / R
   float* gramH = nullptr;    // [M][M][2T+1]: per-atom-pair harmonic inner products (see pair_gram)
+  float* norm2 = nullptr;    // [M]: squared norms of the atoms
   // screened encoder (rsc_screen.h): the screen's format (RSC_FP32: the sizes have no screen)
   rsc_precision scrPrec = RSC_FP32;
   uint16_t* lpA = nullptr;   // stage-1 operand [groups][steps][64][8]
@@ -90,9 +92,9 @@ struct DictBuild {
   int M, B, T, nrows;  // nrows: rows of hat and hatI (16 ceil(M/16))
   int sk[32], kbase[33];   // profiles of harmonic k, start of its block (kbase[T + 1] = B)
   bool bf16;           // the screen's format (else FP16)
-  float *hat, *hatI, *dictA;
+  float *hat, *hatI, *pairs, *dictA;
   uint16_t* lpA;
-  float* gramH;
+  float *gramH, *norm2;
   double* gramH64;
 };
 int launch_dict_tables(const DictBuild& p, void* stream);

@@ -18,8 +18,18 @@ constexpr int screen_ops(int T) { return T + 1 <= 8 ? 1 : 2; }
 constexpr int screen_group_atoms(int T) { return 16 / screen_ops(T); }
 constexpr int screen_steps(int T) { return T + 1 <= 8 ? T + 1 : 8; }   // stage-1 instructions per group
 
-// LDS floats per patch that hold the least-squares state while the screen runs: the factor's
-// strict lower triangle, its inverse diagonal, right-hand sides and coefficients, in float4s.
-constexpr int screen_state_f4(int kmax) { return (kmax * (kmax - 1) / 2 + 3 * kmax + 3) / 4; }
+// Floats of a dictionary row in the screened encoder's LDS: harmonic 0 (padded to an even count),
+// then for each harmonic k >= 1 its profiles as (Re, Im) pairs, so that a pair is one 8-byte read.
+// Every lane reads its own atom's row, and the angle table at its own angle: both strides are
+// twice an odd number of words, so that the lanes spread over all the 8-byte bank pairs (a
+// stride of 56 words takes 8 of the 32, one of 32 words takes 2).
+constexpr int screen_row(int B, int s0) { return B + s0 % 2 + ((B + s0 % 2) / 2 % 2 == 0 ? 2 : 0); }
+constexpr int screen_angle_stride(int T) { return (T + 1) | 1; }   // (cos, sin) pairs per angle
+
+// LDS per patch that holds the least-squares state while the screen runs, in 16-byte units: the
+// factor's strict lower triangle, its inverse diagonal, right-hand sides and coefficients, and
+// the selections, two to a word.  The least-squares step uses the same space for arrays that it
+// indexes at run time (at most 2 kmax words).
+constexpr int screen_state_f4(int kmax) { return (kmax * (kmax - 1) / 2 + 3 * kmax + (kmax + 1) / 2 + 3) / 4; }
 
 }  // namespace rsc
