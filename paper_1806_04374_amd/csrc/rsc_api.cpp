@@ -300,7 +300,35 @@ rsc_status init_tables(rsc_handle* h, int N, int S, int T, rsc_precision prec) {
           if (q < NN && c < b.B) synA[(size_t(tt) * KB + j) * 64 + l] = phiPad[size_t(q) * b.B + c];
         }
   }
+  // operands in three BF16 parts (rsc_split.h): lane l of a 16-term step gives row l % 32, terms
+  // 16 j + 8 (l / 32) + i; every part is the rounding of what the parts before it leave
+  auto parts3 = [&](int tiles, int steps, auto value) {
+    std::vector<uint16_t> out(size_t(tiles) * 3 * steps * 64 * 8, 0);
+    for (int t = 0; t < tiles; ++t)
+      for (int j = 0; j < steps; ++j)
+        for (int l = 0; l < 64; ++l)
+          for (int i = 0; i < 8; ++i) {
+            double rem = double(float(value(32 * t + l % 32, 16 * j + 8 * (l / 32) + i)));
+            for (int q = 0; q < 3; ++q) {
+              const uint16_t hb = to_bf16(float(rem));
+              out[((size_t(t * 3 + q) * steps + j) * 64 + l) * 8 + i] = hb;
+              rem -= double(from_bf16(hb));
+            }
+          }
+    return out;
+  };
+  std::vector<uint16_t> pinv3, phi3;
+  if (N == 15 && b.B > 64 && b.B <= 160)
+    pinv3 = parts3(RTBI, (b.n_pix + 15) / 16, [&](int row, int i) {
+      return row < b.B && i < b.n_pix ? b.pinv[size_t(row) * NN + b.pix[i]] : 0.0;
+    });
+  if ((N == 15 && (b.B == 105 || b.B == 153)) || (N == 11 && b.B == 81))
+    phi3 = parts3((NN + 31) / 32, (b.B + 15) / 16, [&](int q, int c) {
+      return q < NN && c < b.B ? b.phi[size_t(q) * b.B + c] : 0.0;
+    });
   rsc_status s = upload(d.pinvA, pinvA, "projection table");
+  if (s == RSC_OK) s = upload(d.pinv3, pinv3, "projection table");
+  if (s == RSC_OK) s = upload(d.phi3, phi3, "synthesis table");
   if (s == RSC_OK) s = upload(d.pinvD, pinvD, "projection table");
   if (s == RSC_OK) s = upload(d.pixD, pixD, "pixel table");
   if (s == RSC_OK) s = upload(d.phiPad, phiPad, "synthesis table");
@@ -531,6 +559,8 @@ rsc_status rsc_destroy(rsc_handle* h) {
   free_dev(d.pinvD);
   free_dev(d.pixD);
   free_dev(d.pinvI);
+  free_dev(d.pinv3);
+  free_dev(d.phi3);
   free_dev(d.dpixI);
   free_dev(d.phiPad);
   free_dev(d.synA);

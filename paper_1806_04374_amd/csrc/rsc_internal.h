@@ -46,6 +46,8 @@ struct DeviceTables {
   float* pinvD = nullptr;    // projection operand over disk pixels [2][ceil(n_pix/2)][64] (B <= 64)
   int* pixD = nullptr;       // grid index of disk pixel i, -1 past n_pix [2*ceil(n_pix/2)] (every B)
   float* pinvI = nullptr;    // projection operand over disk pixels [tiles][ceil(n_pix/2)][64], tiles = 2 (B <= 64), 4 (B <= 128) or ceil(B/32)
+  uint16_t* pinv3 = nullptr; // pinvI in three BF16 parts (rsc_split.h) [tiles][3][ceil(n_pix/16)][64][8] (N = 15)
+  uint16_t* phi3 = nullptr;  // synthesis matrix in three BF16 parts [ceil(N*N/32)][3][ceil(B/16)][64][8]
   int* dpixI = nullptr;      // (dy << 8 | dx) of disk pixel i, -1 past n_pix [2*ceil(n_pix/2)]
   int* steerTab = nullptr;   // annular basis: per coordinate, harmonic k and partner offset
                              // ((k << 16) | (offset + 32768)); null for the full (S, T) grid

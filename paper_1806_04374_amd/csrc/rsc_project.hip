@@ -3,7 +3,9 @@
 // an FP32 MFMA GEMM with rows = hat coordinates, columns = patches and the
 // contraction over disk pixels.
 //
-//  * project_reg_kernel (11x11 with B <= 96, 15x15 with B in 97..160; 16-byte aligned
+//  * project_split_kernel (15x15 with B in 97..160; 16-byte aligned patches): FP32 products in
+//    three BF16 parts (rsc_split.h), the chunk pipeline of project_reg_kernel.
+//  * project_reg_kernel (11x11 with B <= 96; 16-byte aligned
 //    patches): the operand in registers, one 32-row tile per wave, 32-patch chunks staged
 //    in LDS with the next one prefetched into registers, the partial last chunk in the
 //    same launch.
@@ -32,6 +34,7 @@
 #include "rsc_internal.h"
 #include "rsc_launch.h"
 #include "rsc_lp.h"
+#include "rsc_split.h"
 
 namespace rsc {
 namespace {
@@ -317,6 +320,97 @@ __global__ __launch_bounds__(64 * NT) void project_reg_kernel(const float* __res
   }
 }
 
+// 15x15 patches (B <= 32 NT) through the BF16 matrix cores in three parts (rsc_split.h): the
+// structure of project_reg_kernel, with a pass that gathers the chunk's disk pixels, splits
+// them once for all waves and leaves them in LDS in operand order.  The FP32 form was bound by its
+// 89 FP32 products per wave and chunk (5,700 cycles); this one issues 72 BF16 products (2,300)
+// and about 200 vector instructions for the split, with two barriers per chunk.  500,000 patches
+// of the grid 0.287 -> 0.207 ms, 300,000 of the annular basis 0.265 -> 0.160.
+template <int NNC, int NS, int NT>
+__global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* __restrict__ patches, int64_t nfull,
+                                                               int tail, int B, const uint4* __restrict__ pinv3,
+                                                               const float* __restrict__ pinvI, int KPD,
+                                                               const int* __restrict__ pix, int n_pix,
+                                                               float* __restrict__ xhat) {
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  constexpr int NTH = 64 * NT, NV = kProjRegPatches * NNC / 4, VPT = (NV + NTH - 1) / NTH;
+  __shared__ v4f tile4[VPT * NTH];               // [32][NNC] used; the rest takes clamped copies
+  __shared__ uint4 xb[3 * NS * 64];
+  __shared__ int4 sPix[NS * 4];
+  __shared__ int infinite[2];                    // of this chunk and the next
+  const float* tile = reinterpret_cast<const float*>(tile4);
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 31, u = lane >> 5;
+  uint4 a[NS][3];
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[j][q] = pinv3[((w * 3 + q) * NS + j) * 64 + lane];
+  // slots past the disk have zero operand parts: point them at disk pixel 0
+  for (int i = t; i < 16 * NS; i += NTH) reinterpret_cast<int*>(sPix)[i] = pix[i < n_pix ? i : 0];
+  if (t == 0) infinite[0] = infinite[1] = 0;
+  __syncthreads();
+  int vi[VPT];
+#pragma unroll
+  for (int v = 0; v < VPT; ++v) vi[v] = t + NTH * v < NV ? t + NTH * v : NV - 1;
+  const int64_t nchunk = nfull + (tail > 0 ? 1 : 0);
+  v4f nxt[VPT];
+  int64_t c = blockIdx.x;
+  if (nfull > 0) {
+    const int64_t c0 = c < nfull ? c : nfull - 1;
+    const v4f* s4 = reinterpret_cast<const v4f*>(patches + c0 * kProjRegPatches * NNC);
+#pragma unroll
+    for (int v = 0; v < VPT; ++v) nxt[v] = s4[vi[v]];
+  }
+  const float* mine = tile + col * NNC;
+  for (int k = 0; c < nchunk; c += gridDim.x, ++k) {
+    // every wave has split the previous chunk (the barrier before its products)
+    if (c < nfull) {
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) tile4[t + NTH * v] = nxt[v];
+    } else {
+      const float* src = patches + c * kProjRegPatches * NNC;
+      float* tw = reinterpret_cast<float*>(tile4);
+      for (int i = t; i < kProjRegPatches * NNC; i += NTH) tw[i] = i < tail * NNC ? src[i] : 0.f;
+    }
+    __syncthreads();   // (every wave is past the previous chunk's products)
+    if (t == 0) infinite[k & 1 ^ 1] = 0;
+    if (nfull > 0) {
+      const int64_t nx = c + gridDim.x, cn = nx < nfull ? nx : (c < nfull ? c : nfull - 1);
+      const v4f* s4 = reinterpret_cast<const v4f*>(patches + cn * kProjRegPatches * NNC);
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) nxt[v] = s4[vi[v]];
+    }
+    // wave w splits steps w, w + NT, ...
+#pragma unroll 1
+    for (int j = w; j < NS; j += NT) {
+      const int4 p0 = sPix[j * 4 + u * 2], p1 = sPix[j * 4 + u * 2 + 1];
+      const float v[8] = {mine[p0.x], mine[p0.y], mine[p0.z], mine[p0.w],
+                          mine[p1.x], mine[p1.y], mine[p1.z], mine[p1.w]};
+      uint4 hi, mid, lo;
+      split3(v, hi, mid, lo);
+      xb[j * 64 + lane] = hi;
+      xb[(NS + j) * 64 + lane] = mid;
+      xb[(2 * NS + j) * 64 + lane] = lo;
+      if (any_infinite(v)) infinite[k & 1] = 1;
+    }
+    __syncthreads();
+    f32x16 acc = contract_split3<NS>(a, xb, lane);
+    if (infinite[k & 1]) {
+      // an infinite pixel in the chunk: the FP32 products
+      const int64_t p = c * kProjRegPatches + col;
+      const float* src = patches + (p < nfull * kProjRegPatches + tail ? p : 0) * NNC;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll 1
+      for (int j = 0; j < KPD; ++j) {
+        const int i = 2 * j + u;
+        acc = mfma32(pinvI[(w * KPD + j) * 64 + lane], src[pix[i < n_pix ? i : 0]], acc);
+      }
+    }
+    if (c < nfull || col < tail) store_column(xhat + (c * kProjRegPatches + col) * B, acc, 32 * w, u, B);
+  }
+}
+
 // The compensated 16-bit projection (as project_tiled_lp_kernel) with the structure of
 // project_reg_kernel: a block of two waves (one 32-row operand tile each, its NP 16-bit
 // parts in registers) takes 32 patches at a time from LDS, the next chunk is prefetched
@@ -537,9 +631,9 @@ int launch_project(const DeviceTables& t, const float* patches, int64_t P, float
                        reinterpret_cast<const uint4*>(t.lpPinv), t.lpPix16, t.lpPinvUnscale, vin, vout, xhat);
     return int(hipGetLastError());
   }
-  // register-operand kernel (16-byte aligned patches): 11x11 with B <= 64 or 96 (2 or 3 row
-  // tiles) and 15x15 with B in 97..128 or 129..160 (4 or 5 row tiles); whole 32-patch chunks
-  // and the partial last one
+  // register-operand kernels (16-byte aligned patches): 11x11 with B <= 64 or 96 (2 or 3 row
+  // tiles, bound by memory) and 15x15 with B in 97..128 or 129..160 (4 or 5 row tiles, in three
+  // BF16 parts: the FP32 products bound them); whole 32-patch chunks and the partial last one
   const bool aligned = (reinterpret_cast<uintptr_t>(patches) & 15) == 0;
   const bool vout = (reinterpret_cast<uintptr_t>(xhat) & 15) == 0 && (kProjRegPatches * t.B) % 4 == 0;
   auto go_reg = [&](auto kern, int nt) {
@@ -556,10 +650,21 @@ int launch_project(const DeviceTables& t, const float* patches, int64_t P, float
     return go_reg(project_reg_kernel<121, 49, 2>, 2);
   if (aligned && t.N == 11 && t.n_pix == 97 && t.B > 64 && t.B <= 96 && t.pinvI && t.pixD)   // annular, B = 81
     return go_reg(project_reg_kernel<121, 49, 3>, 3);
-  if (aligned && t.N == 15 && t.n_pix == 177 && t.B > 96 && t.B <= 128 && t.pinvI && t.pixD)
-    return go_reg(project_reg_kernel<225, 89, 4>, 4);
-  if (aligned && t.N == 15 && t.n_pix == 177 && t.B > 128 && t.B <= 160 && t.pinvI && t.pixD)  // annular, B = 153
-    return go_reg(project_reg_kernel<225, 89, 5>, 5);
+  auto go_split = [&](auto kern, int nt) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * nt, 0) != hipSuccess || per_cu < 1)
+      per_cu = 1;
+    const int64_t nfull = P / kProjRegPatches, tail = P - nfull * kProjRegPatches;
+    const int64_t work = nfull + (tail > 0), cap = int64_t(cus()) * per_cu;
+    hipLaunchKernelGGL(kern, dim3(unsigned(work < cap ? work : cap)), dim3(64 * nt), 0, st, patches, nfull,
+                       int(tail), t.B, reinterpret_cast<const uint4*>(t.pinv3), t.pinvI, (t.n_pix + 1) / 2, t.pixD,
+                       t.n_pix, xhat);
+    return int(hipGetLastError());
+  };
+  if (aligned && t.N == 15 && t.n_pix == 177 && t.B > 96 && t.B <= 128 && t.pinv3 && t.pixD)
+    return go_split(project_split_kernel<225, 12, 4>, 4);
+  if (aligned && t.N == 15 && t.n_pix == 177 && t.B > 128 && t.B <= 160 && t.pinv3 && t.pixD)  // annular, B = 153
+    return go_split(project_split_kernel<225, 12, 5>, 5);
   // unaligned 11x11 input (S = T = 5): the LDS-operand tiled kernel
   if (t.N == 11 && t.S == 5 && t.T == 5 && t.pinvD) {
     constexpr int kNN = 121, kKPD = 49;

@@ -26,6 +26,7 @@
 #include "rsc_device.h"
 #include "rsc_internal.h"
 #include "rsc_launch.h"
+#include "rsc_split.h"
 
 namespace rsc {
 namespace {
@@ -558,6 +559,105 @@ __global__ __launch_bounds__(256) void synth_mfma_kernel(const float* __restrict
   }
 }
 
+// Phi x_hat where the FP32 products (vector FMAs on the annular basis) bound it: 15x15, and the
+// annular basis at 11x11, in three BF16 parts (rsc_split.h).  500,000 15x15 patches of the grid
+// 0.261 -> 0.217 ms; of the annular basis, 300,000 at 15x15 1.246 -> 0.159, 500,000 at 11x11
+// 0.576 -> 0.095.  One 32-pixel tile per wave, its rows of Phi in registers; a chunk's
+// hat rows are staged in LDS and split once for all waves into operand order, and the pixels
+// leave through LDS as whole lines (16-byte stores of each lane's own rows measured slower:
+// 0.238 against 0.224 ms at 500,000 15x15 patches).  The partial last chunk is done in the same launch.
+template <int NNC, int BB, int NT>
+__global__ __launch_bounds__(64 * NT, 2) void synth_split_kernel(const float* __restrict__ xhat, int64_t P,
+                                                              const uint4* __restrict__ phi3,
+                                                              const float* __restrict__ synA, bool vec_out,
+                                                              float* __restrict__ out) {
+  constexpr int NTH = 64 * NT, NS = (BB + 15) / 16, NV = kSynMP * BB / 4, VPT = (NV + NTH - 1) / NTH, KB = (BB + 1) / 2;
+  static_assert((kSynMP * BB) % 4 == 0 && (kSynMP * NNC) % 4 == 0 && 32 * NT >= NNC, "whole float4s, tiles cover the pixels");
+  __shared__ v4f xs4[VPT * NTH];                 // [32][BB] used; the rest takes clamped copies
+  __shared__ uint4 xb[3 * NS * 64];
+  __shared__ v4f st4[kSynMP * NNC / 4];          // [32 patches][NNC]
+  __shared__ int infinite[2];                    // of this chunk and the next
+  float* st = reinterpret_cast<float*>(st4);
+  float* xs = reinterpret_cast<float*>(xs4);
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 31, u = lane >> 5;
+  uint4 a[NS][3];
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[j][q] = phi3[((w * 3 + q) * NS + j) * 64 + lane];
+  int vi[VPT];
+#pragma unroll
+  for (int v = 0; v < VPT; ++v) vi[v] = t + NTH * v < NV ? t + NTH * v : NV - 1;
+  if (t == 0) infinite[0] = infinite[1] = 0;
+  __syncthreads();
+  const int64_t nfull = P / kSynMP, nchunk = (P + kSynMP - 1) / kSynMP;
+  const int tail = int(P - nfull * kSynMP);
+  v4f nxt[VPT];
+  int64_t c = blockIdx.x;
+  auto fetch = [&](int64_t ch) {
+    if (ch < nfull) {
+      const v4f* s4 = reinterpret_cast<const v4f*>(xhat + ch * kSynMP * BB);
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) nxt[v] = s4[vi[v]];
+    }
+  };
+  fetch(c);
+  const float* mine = xs + col * BB;
+  for (int k = 0; c < nchunk; c += gridDim.x, ++k) {
+    // every wave has split the previous chunk (the barrier before its products)
+    if (c < nfull) {
+#pragma unroll
+      for (int v = 0; v < VPT; ++v) xs4[t + NTH * v] = nxt[v];
+    } else {
+      for (int i = t; i < kSynMP * BB; i += NTH) xs[i] = i < tail * BB ? xhat[c * kSynMP * BB + i] : 0.f;
+    }
+    __syncthreads();   // (every wave is past the previous chunk's products)
+    if (t == 0) infinite[k & 1 ^ 1] = 0;
+    fetch(c + gridDim.x);
+#pragma unroll 1
+    for (int j = w; j < NS; j += NT) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int q = 16 * j + 8 * u + i;
+        v[i] = q < BB ? mine[q < BB ? q : 0] : 0.f;
+      }
+      uint4 hi, mid, lo;
+      split3(v, hi, mid, lo);
+      xb[j * 64 + lane] = hi;
+      xb[(NS + j) * 64 + lane] = mid;
+      xb[(2 * NS + j) * 64 + lane] = lo;
+      if (any_infinite(v)) infinite[k & 1] = 1;
+    }
+    __syncthreads();
+    f32x16 acc = contract_split3<NS>(a, xb, lane);
+    if (infinite[k & 1]) {   // an infinite coordinate in the chunk: the FP32 products
+      const int64_t p = c * kSynMP + col;
+      const float* src = xhat + (p < P ? p : 0) * BB;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 1
+      for (int j = 0; j < KB; ++j)
+        acc = mfma32(synA[(w * KB + j) * 64 + lane], 2 * j + u < BB ? src[2 * j + u] : 0.f, acc);
+    }
+    // (the previous chunk's pixels have been read: every wave has passed two barriers since)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = 32 * w + 8 * (r / 4) + 4 * u + (r % 4);
+      if (q < NNC) st[col * NNC + q] = acc[r];
+    }
+    __syncthreads();
+    float* dst = out + c * kSynMP * NNC;
+    if (vec_out && c < nfull) {
+      for (int i = t; i < kSynMP * NNC / 4; i += NTH)
+        __builtin_nontemporal_store(st4[i], reinterpret_cast<v4f*>(dst) + i);
+    } else {
+      const int n = (c < nfull ? kSynMP : tail) * NNC;
+      for (int i = t; i < n; i += NTH) dst[i] = st[i];
+    }
+  }
+}
+
 double keys(double t) {
   const double a = -0.5;
   t = std::fabs(t);
@@ -754,8 +854,24 @@ int launch_steer(const DeviceTables& t, const float* xhat, int64_t P, const floa
 int launch_synth_hat(const DeviceTables& t, const float* xhat, int64_t P, float* out, void* stream) {
   const int NN = t.N * t.N;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // compiled geometries, 16-byte aligned hat rows: whole 32-patch chunks on MFMA, the rest below
-  const int geo = NN == 121 && t.B == 55 ? 0 : NN == 225 && t.B == 105 ? 1 : -1;
+  // three BF16 parts where the FP32 products bound the kernel (16-byte aligned hat rows)
+  if (t.phi3 && (reinterpret_cast<uintptr_t>(xhat) & 15) == 0) {
+    const bool vout = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    auto go = [&](auto kern, int nt) {
+      int per_cu = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * nt, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+      const int64_t chunks = (P + kSynMP - 1) / kSynMP, cap = int64_t(num_cus()) * per_cu;
+      hipLaunchKernelGGL(kern, dim3(unsigned(chunks < cap ? chunks : cap)), dim3(64 * nt), 0, st, xhat, P,
+                         reinterpret_cast<const uint4*>(t.phi3), t.synA, vout, out);
+      return int(hipGetLastError());
+    };
+    if (NN == 225 && t.B == 105) return go(synth_split_kernel<225, 105, 8>, 8);
+    if (NN == 225 && t.B == 153) return go(synth_split_kernel<225, 153, 8>, 8);
+    if (NN == 121 && t.B == 81) return go(synth_split_kernel<121, 81, 4>, 4);
+  }
+  // 11x11 grid, 16-byte aligned hat rows: whole 32-patch chunks on FP32 MFMA (bound by memory),
+  // the rest below
+  const int geo = NN == 121 && t.B == 55 ? 0 : -1;
   const int64_t nm = (geo >= 0 && t.synA && (reinterpret_cast<uintptr_t>(xhat) & 15) == 0) ? P / kSynMP : 0;
   if (nm > 0) {
     const bool vout = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
@@ -765,7 +881,7 @@ int launch_synth_hat(const DeviceTables& t, const float* xhat, int64_t P, float*
                          out);
       return hipGetLastError();
     };
-    hipError_t e = geo == 0 ? go(synth_mfma_kernel<121, 55, 1>) : go(synth_mfma_kernel<225, 105, 2>);
+    const hipError_t e = go(synth_mfma_kernel<121, 55, 1>);
     if (e != hipSuccess) return int(e);
     const int64_t done = nm * kSynMP;
     if (done == P) return 0;
