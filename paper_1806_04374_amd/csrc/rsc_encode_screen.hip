@@ -40,6 +40,7 @@ int screen_waves(const DeviceTables& t, int kmax) {
 }
 
 bool screen_usable(const DeviceTables& t, int K) {
+  if (t.geo != kGeoGrid && K > kAnnularMaxK) return false;   // no instance has that many slots
   return t.scrPrec != RSC_FP32 && screen_waves(t, kmax_of(t, K)) > 0;
 }
 

@@ -145,3 +145,14 @@ def test_screen_agrees_with_fp32_tile(dev, kind, N, M, R, K):
     assert int((~same).sum()) <= 20     # 99.9%; a handful of ties in 1e5 steps are expected
     assert float((a[2] - b[2])[same].abs().max()) <= 1e-4 * float(b[2].abs().max())
     h.close()
+
+
+def test_autotune_refuses_annular_beyond_four(dev):
+    """No form of the pursuit on the annular basis is compiled for K > 4: refused before any launch."""
+    from paper_1806_04374_amd import rsc
+    h = rsc.rsc_create_annular(11)
+    d = np.random.default_rng(1).standard_normal((8, h.B)).astype(np.float32)
+    rsc.rsc_set_dictionary(h, d / np.linalg.norm(d, axis=1, keepdims=True), 32)
+    x = torch.randn((100, h.B), device=dev)
+    with pytest.raises(rsc.RscError):
+        rsc.rsc_autotune_encode(h, x, 5)
