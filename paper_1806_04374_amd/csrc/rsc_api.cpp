@@ -829,6 +829,24 @@ rsc_status rsc_set_launch(rsc_handle* h, rsc_tile tile, int blocks_per_cu) {
   return ok();
 }
 
+// Tile shape of the FP32 encoder: RSC_TILE_32 when asked for (or, under RSC_TILE_AUTO, when
+// R > 32) and compiled for the geometry and K; else RSC_TILE_16.  With R <= 32 the 32x32
+// tile's 32 angle rows are half empty (R/2 <= 16 rows after the parity split), and the 16x16
+// tile does less work per patch and runs twice as many waves.
+int encoder_tile(const rsc_handle* h, rsc_tile tile, int K) {
+  const bool want32 = tile == RSC_TILE_32 || (tile == RSC_TILE_AUTO && h->dev.R > 32);
+  return want32 && rsc::tile32_usable(h->dev, K) ? RSC_TILE_32 : RSC_TILE_16;
+}
+
+// The screened encoder, and for FP32 handles the full one over the patches that it marked: those
+// with a selection that FP32 rounding decides.
+int encode_screened(const rsc_handle* h, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
+                    float* coef, float* resid2, void* stream) {
+  const int e = rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, resid2, stream);
+  if (e || !rsc::screen_resolves(h->dev, K)) return e;
+  return rsc::launch_encode(h->dev, encoder_tile(h, RSC_TILE_AUTO, K), xhat, P, K, atom, angle, coef, resid2, stream, true);
+}
+
 rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int K, int32_t* atom,
                                int32_t* angle, float* coef, int reps, double* report, int* n_report,
                                void* stream) {
@@ -848,7 +866,7 @@ rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int 
   const int ntiles = (!lp && rsc::tile32_usable(h->dev, K)) ? 2 : 1;
   auto run = [&](int tile) {
     return lp || (screened && tile == RSC_TILE_AUTO)
-               ? rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, nullptr, stream)
+               ? encode_screened(h, xhat, P, K, atom, angle, coef, nullptr, stream)
                : rsc::launch_encode(h->dev, tile, xhat, P, K, atom, angle, coef, nullptr, stream);
   };
   hipEvent_t e0, e1;
@@ -906,15 +924,6 @@ rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int 
   return ok();
 }
 
-// Tile shape of the FP32 encoder: RSC_TILE_32 when asked for (or, under RSC_TILE_AUTO, when
-// R > 32) and compiled for the geometry and K; else RSC_TILE_16.  With R <= 32 the 32x32
-// tile's 32 angle rows are half empty (R/2 <= 16 rows after the parity split), and the 16x16
-// tile does less work per patch and runs twice as many waves.
-int encoder_tile(const rsc_handle* h, int K) {
-  const bool want32 = h->tile == RSC_TILE_32 || (h->tile == RSC_TILE_AUTO && h->dev.R > 32);
-  return want32 && rsc::tile32_usable(h->dev, K) ? RSC_TILE_32 : RSC_TILE_16;
-}
-
 // Whether the pursuit of K atoms runs the screened encoder: every 16-bit handle, and FP32 handles
 // under RSC_TILE_AUTO where it is compiled (M <= 128, R <= 64, its tables within the LDS).  It
 // depends on the handle and K only, never on P, so a patch's code does not depend on its launch.
@@ -931,7 +940,7 @@ rsc_status rsc_encode_info(const rsc_handle* h, int K, int* tile, double* mfma_f
     if (mfma_flops_per_patch) *mfma_flops_per_patch = rsc::screen_mfma_flops_per_patch(h->dev, K);
     return ok();
   }
-  const int t = encoder_tile(h, K);
+  const int t = encoder_tile(h, h->tile, K);
   if (tile) *tile = t;
   if (mfma_flops_per_patch) *mfma_flops_per_patch = rsc::encode_mfma_flops_per_patch(h->dev, t, K);
   return ok();
@@ -971,9 +980,9 @@ rsc_status rsc_omp_encode(const rsc_handle* h, const float* xhat, int64_t P, int
   if (rsc_status f = check_fault(h)) return f;
   if (encoder_screened(h, K))
     return dict_launch(h, stream, "encode launch", [&] {
-      return rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, resid2, stream);
+      return encode_screened(h, xhat, P, K, atom, angle, coef, resid2, stream);
     });
-  const int tile = encoder_tile(h, K);
+  const int tile = encoder_tile(h, h->tile, K);
   return dict_launch(h, stream, "encode launch", [&] {
     return rsc::launch_encode(h->dev, tile, xhat, P, K, atom, angle, coef, resid2, stream);
   });

@@ -55,6 +55,7 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
   constexpr int NKS = L::NKS, NQ = L::NQ, B = L::B;
   extern __shared__ float lds[];
   const int R = prm.R, M = prm.M, K = prm.K, HALF = prm.R / 2;
+  if (prm.marked && !enc::block_has_mark<32>(prm, 4)) return;
   float* sA = lds;                       // [NG][NKS][64]
   float* sHat = sA + NG * NKS * 64;      // [NG*16][B]
   float* sCs = sHat + NG * 16 * B;       // [2][NQ][R]
@@ -74,9 +75,8 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
 #pragma unroll
   for (int q = 0; q < NQ; ++q) F[q] = prm.dftA[q * 64 + lane];
 
-  const int64_t nwt = (prm.P + 31) / 32;
-  for (int64_t wt = int64_t(blockIdx.x) * 4 + wave; wt < nwt; wt += int64_t(gridDim.x) * 4) {
-    const int64_t p = wt * 32 + col;
+  enc::WavePatches<32> tiles(prm, 4, wave);
+  for (int64_t p; tiles.next(lane, p);) {
     const bool valid = p < prm.P;
     float res[NKS];
     static_for<NKS>([&](auto J) {
@@ -327,19 +327,19 @@ double encode_mfma_flops_per_patch(const DeviceTables& t, int tile, int K) {
 }
 
 int launch_encode(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
-                  int32_t* angle, float* coef, float* resid2, void* stream) {
+                  int32_t* angle, float* coef, float* resid2, void* stream, bool marked) {
   if (P <= 0) return 0;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (tile == RSC_TILE_32) {
     if (!tile32_usable(t, K)) return int(hipErrorInvalidValue);
     EncodeParams prm{xhat, P, K, t.M, t.R, t.dictA, t.dictHat, t.dftA32, t.cs, t.gramH, t.gramH64, t.cs64,
-                     atom, angle, coef, resid2, t.lpStats, nullptr};
+                     atom, angle, coef, resid2, t.lpStats, nullptr, marked};
     return r32(t, prm, st);
   }
   EncodeParams prm{xhat, P, K, t.M, t.R, nullptr, t.dictHat, t.R % 2 == 0 ? t.dftA16s : t.dftA16, t.cs, t.gramH,
-                   t.gramH64, t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI};
+                   t.gramH64, t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI, marked};
   if (t.geo == kGeoAnnular11 || t.geo == kGeoAnnular15)
-    return launch_encode_annular(t, xhat, P, K, atom, angle, coef, resid2, stream);
+    return launch_encode_annular(t, xhat, P, K, atom, angle, coef, resid2, stream, marked);
   if (t.geo != kGeoGrid) return int(hipErrorInvalidValue);
   if (t.S == 5 && t.T == 5) return r16<UniformCounts<5, 5>>(t, prm, st);
   if (t.S == 7 && t.T == 7) return r16<UniformCounts<7, 7>>(t, prm, st);

@@ -29,7 +29,61 @@ struct EncodeParams {
   float* resid2;
   unsigned long long* stats;   // [4]: [3] counts pursuit steps solved in FP64
   const float* dictHatI;       // i * dictionary rows, as dictHat (16x16 tile with IROWS; else unused)
+  bool marked;                 // code only the patches whose first atom is kTieMark
 };
+
+// The patches of a wave, TP at a time: its tiles wt, wt + stride, ... in turn, or (marked) the
+// marked patches of these tiles gathered, so that a wave with few of them runs one tile's pursuit
+// for all of them (images of 2.3M windows, 128 atoms, 6 steps: the launch takes 0.40 ms, the
+// latency of one tile's pursuit is 0.24).
+template <int TP>
+struct WavePatches {
+  const EncodeParams& prm;
+  int64_t wt, stride, base = 0;
+  unsigned long long rest = 0;   // marked patches of the tiles from base on that were not yet given
+  __device__ __forceinline__ WavePatches(const EncodeParams& prm, int NW, int wave)
+      : prm(prm), wt(int64_t(blockIdx.x) * NW + wave), stride(int64_t(gridDim.x) * NW) {}
+  // Sets this lane's patch (P or beyond: none); false after the last.
+  __device__ __forceinline__ bool next(int lane, int64_t& p) {
+    const int64_t nwt = (prm.P + TP - 1) / TP;
+    if (!prm.marked) {
+      p = wt * TP + lane % TP;
+      wt += stride;
+      return wt - stride < nwt;
+    }
+    p = prm.P;
+    int n = 0;
+    while (n < TP) {
+      if (rest == 0) {           // the marks of 64 / TP tiles at once
+        if (wt >= nwt) break;
+        base = wt;
+        const int64_t q = (wt + lane / TP * stride) * TP + lane % TP;
+        rest = __ballot(q < prm.P && prm.atom[q * prm.K] == kTieMark);
+        wt += 64 / TP * stride;
+        continue;
+      }
+      const int b = __builtin_ctzll(rest);
+      rest &= rest - 1;
+      if (lane % TP == n) p = (base + b / TP * stride) * TP + b % TP;
+      ++n;
+    }
+    return n > 0;
+  }
+};
+
+// Whether any patch of this block's tiles is marked: TP patches per tile, tile wt to wave wt % NW of
+// its block.  Every thread reads patches of its own, so the scan has the block's loads in flight
+// at once; a block without a mark ends before it fills its tables.
+template <int TP>
+__device__ __forceinline__ bool block_has_mark(const EncodeParams& prm, int NW) {
+  const int64_t per = int64_t(NW) * TP, step = per * gridDim.x;
+  bool any = false;
+#pragma unroll 4
+  for (int64_t b = int64_t(blockIdx.x) * per + threadIdx.x % per + threadIdx.x / per * step; b < prm.P;
+       b += blockDim.x / per * step)
+    any |= prm.atom[b * prm.K] == kTieMark;
+  return __syncthreads_or(any);
+}
 
 // Adds this wave's count of FP64 least-squares steps to stats[3] (one atomic per wave).
 __device__ __forceinline__ void count_fp64(unsigned long long* stats, unsigned n, int lane) {
@@ -125,6 +179,7 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
   extern __shared__ float lds[];
   const int R = prm.R, M = prm.M, K = prm.K, HALF = SPLIT ? prm.R / 2 : prm.R;
   const int NG = (M + 7) / 8;
+  if (prm.marked && !block_has_mark<16>(prm, NW)) return;
   float* sHat = lds;                              // [NG*8][B]
   float* sHatI = sHat + (IROWS ? NG * 8 * B : 0);  // [NG*8][B] with IROWS
   float* sCs = sHatI + NG * 8 * B;                // [2][NQ][R]
@@ -162,9 +217,8 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
   auto k1_of = [](int q) { return SPLIT ? (q < SE ? 4 * q : 4 * (q - SE) + 1) : 2 * q; };
   auto k2_of = [](int q) { return SPLIT ? (q < SE ? 4 * q + 2 : 4 * (q - SE) + 3) : 2 * q + 1; };
 
-  const int64_t nwt = (prm.P + 15) / 16;
-  for (int64_t wt = int64_t(blockIdx.x) * NW + wave; wt < nwt; wt += int64_t(gridDim.x) * NW) {
-    const int64_t p = wt * 16 + col;
+  WavePatches<16> tiles(prm, NW, wave);
+  for (int64_t p; tiles.next(lane, p);) {
     const bool valid = p < prm.P;
     float res[NKS];
     static_for<NKS>([&](auto J) {

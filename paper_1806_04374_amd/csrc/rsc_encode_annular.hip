@@ -38,11 +38,11 @@ int dispatchA(const DeviceTables& t, const enc::EncodeParams& prm, hipStream_t s
 }  // namespace
 
 int launch_encode_annular(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom,
-                          int32_t* angle, float* coef, float* resid2, void* stream) {
+                          int32_t* angle, float* coef, float* resid2, void* stream, bool marked) {
   if (P <= 0) return 0;
   if (K < 1 || K > kAnnularMaxK || t.R % 2 != 0 || t.R > kAnnularMaxR) return int(hipErrorInvalidValue);
   const enc::EncodeParams prm{xhat, P, K, t.M, t.R, nullptr, t.dictHat, t.dftA16s, t.cs, t.gramH, t.gramH64,
-                              t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI};
+                              t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI, marked};
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (t.geo == kGeoAnnular11) return dispatchA<AnnularCounts11>(t, prm, st);
   if (t.geo == kGeoAnnular15) return dispatchA<AnnularCounts15>(t, prm, st);

@@ -29,6 +29,9 @@
 //     maxima are kept for this as FP16 fractions of ||r|| in private memory, which is read only
 //     for candidates, with a margin of 2^-10 for their rounding.  FP16's window holds about one
 //     atom, and the bookkeeping would cost more than it saves.
+//   ties (FP32 handles, ScreenParams::tie): where another atom or angle comes within the rounding
+//     of the FP32 sums, the patch is marked and the full FP32 encoder codes it in a second launch
+//     (the rule and its figures: screen_resolves, rsc_encode_screen.hip).
 //   least squares and residual update in FP32 (ls_step), as in the FP32 encoders.
 //
 // What bounds it: vector issue.  A wave's maxima over 64 angles cost 16 three-way maxima per
@@ -69,6 +72,7 @@ struct ScreenParams {
   unsigned long long* stats;   // [4], see rsc_precision_stats
   float cond_max;              // least squares in FP64 beyond this bound (ls_update)
   bool count;                  // whether candidates are counted (16-bit handles)
+  float tie;                   // > 0: patches with a selection decided by less than tie ||r|| get kTieMark
 };
 
 // The least-squares state of the wave's 32 patches in LDS: float4 q of patch col at
@@ -454,6 +458,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
     init_state(st, valid);
     LsState<KMAX> ls;
     init_ls(ls);
+    bool tied = false;
 
     for (int it = 0; it < K; ++it) {
       const float n2 = norm2<L>(res);
@@ -584,7 +589,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       if (kFilter && has1 && (m1 & 1) == u) mask &= ~(uint64_t(1) << (m1 >> 1));
 
       // ---------------- FP32 scores of the candidates, in increasing atom order (after the first)
-      float best = -1.f;
+      float best = -1.f, second = -1.f;   // the largest and the second largest of the atoms' maxima
       int bm = 0;
       unsigned nc = 0;
       f32x16 E[FT], O;
@@ -632,6 +637,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         cm = max_halves_nonneg(cm);
         // equal maxima go to the smaller atom (without the filter the atoms come in order)
         const bool gt = has && (cm > best || (kFilter && cm == best && mc < bm));
+        if (!kFilter) second = has ? __builtin_amdgcn_fmed3f(best, cm, second) : second;   // second <= best
         best = gt ? cm : best;
         bm = gt ? mc : bm;
 #pragma unroll
@@ -658,8 +664,9 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       // maximum.  max(|E| + |O|) is bit for bit the largest rounded |E + O| or |E - O|, so the
       // scores are compared with it for equality; rows past the valid angles score 0 and come
       // last.  The rows ascend with the register in each half-wave: searched from the last.
-      int rs = 0x7fffffff;
+      int rs = 0x7fffffff, near = 0;       // near: angles whose |score| is at least thr
       float cval = 0.f;
+      const float thr = best - prm.tie * rn;
       if (SPLIT) {
         const int HALF = R / 2;
 #pragma unroll
@@ -669,6 +676,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
             const float s = h == 0 ? E[0][i] + O[i] : E[0][i] - O[i];
             const bool eq = fabsf(s) == best;
             rs = eq ? 8 * (i / 4) + (i % 4) + 4 * u + h * HALF : rs;
+            if (!kFilter) near += fabsf(s) >= thr ? 1 : 0;
             cval = eq ? s : cval;
           }
       } else {
@@ -679,6 +687,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
             const float s = E[t][i];
             const bool eq = fabsf(s) == best;
             rs = eq ? 32 * t + 8 * (i / 4) + (i % 4) + 4 * u : rs;
+            if (!kFilter) near += fabsf(s) >= thr ? 1 : 0;
             cval = eq ? s : cval;
           }
       }
@@ -688,6 +697,30 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         cval = oc < rs ? ov : cval;
         rs = oc < rs ? oc : rs;
         rs = rs < R ? rs : R - 1;
+      }
+      // ---------------- whether another atom, or another angle of the best one, comes within the
+      // rounding of these sums.  Angles that tie at the spacing R / near are the symmetry of the
+      // atom (or of the patch) itself: any of them gives the same code, and the first one is kept
+      if (!kFilter && prm.tie > 0.f) {
+        near += other_half(near, u);
+        tied = tied || (st.active && second >= thr);
+        if (__any(st.active && near > 1)) {
+          int lo = 0x7fffffff, hi = -1;
+          float thr2 = thr;
+          asm volatile("" : "+v"(thr2));   // compared again: 32 masks kept from above would spill
+#pragma unroll
+          for (int t = 0; t < (SPLIT ? 2 : FT); ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const float s = SPLIT ? (t == 0 ? E[0][i] + O[i] : E[0][i] - O[i]) : E[t % FT][i];
+              const int r = 8 * (i / 4) + (i % 4) + 4 * u + t * (SPLIT ? R / 2 : 32);
+              lo = fabsf(s) >= thr2 ? min(lo, r) : lo;
+              hi = fabsf(s) >= thr2 ? max(hi, r) : hi;
+            }
+          lo = min(lo, other_half(lo, u));
+          hi = max(hi, other_half(hi, u));
+          tied = tied || (st.active && near > 1 && hi - lo != R - R / near);
+        }
       }
       // ---------------- least squares
       wave_lds_order();
@@ -705,7 +738,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       for (int i = 0; i < KMAX; ++i) {
         if (i < K) {
           const bool s = i < st.nsel;
-          prm.atom[p * K + i] = s ? st.selm[i] : -1;
+          prm.atom[p * K + i] = i == 0 && tied ? kTieMark : s ? st.selm[i] : -1;
           prm.angle[p * K + i] = s ? st.selr[i] : -1;
           prm.coef[p * K + i] = s ? st.cf[i] : 0.f;
         }

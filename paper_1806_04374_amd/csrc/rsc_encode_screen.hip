@@ -22,6 +22,20 @@ size_t table_bytes(const DeviceTables& t) {
   return screen::screen_table_bytes(ng, screen_steps(t.T), t.T + 1, ng * ag, screen_row(t.B, t.sk[0]), t.R, ft);
 }
 
+// Ties.  Two scores closer than the rounding of their FP32 sums are ordered by that rounding, and a
+// patch's code differs from there on by which form summed them: 8 to 16 of 2.3M image windows
+// (128 atoms, 6 steps), 0 to 4 of 10^6 patches (64 atoms, 4 steps), where also the two full tile
+// shapes disagree, and some coefficients then differ by their whole size.  FP32 handles
+// therefore leave such patches to the full encoder, which codes them from the start: a step
+// is marked when another atom or angle comes within 2^-22 ||r|| of the selected one.  Of 28M image
+// windows none differed any more, where without it about 130 do; the gaps that flip are of the
+// size of the summation error, about 0.3 of that.
+// The second launch costs about 3 us where nothing is marked and the latency of one tile's pursuit
+// (100 us, 240 us at 15x15 with 6 steps) where something is, so it is left out where the ties are
+// rare: for M K below 128 (one atom of a class dictionary, or the few atoms of a small call).
+constexpr float kTieWindow = 0x1p-22f;
+constexpr int kTieWork = 128;
+
 }  // namespace
 
 bool screen_supported(int geo, int S, int T, int M, int R) {
@@ -44,6 +58,8 @@ bool screen_usable(const DeviceTables& t, int K) {
   return t.scrPrec != RSC_FP32 && screen_waves(t, kmax_of(t, K)) > 0;
 }
 
+bool screen_resolves(const DeviceTables& t, int K) { return t.prec == RSC_FP32 && t.M * K >= kTieWork; }
+
 double screen_mfma_flops_per_patch(const DeviceTables& t, int K) {
   // per step and 32 patches: the stage-1 and stage-2 32x32x16 instructions of every group
   const int ag = screen_group_atoms(t.T), ops = screen_ops(t.T), ng = (t.M + ag - 1) / ag, rt = t.R <= 32 ? 1 : 2;
@@ -58,7 +74,8 @@ int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, in
                                  reinterpret_cast<const uint4*>(t.lpA), t.dictPairs, t.dictHat,
                                  reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.norm2, t.gramH64, t.cs64,
                                  atom, angle, coef, resid2, t.lpStats,
-                                 t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32};
+                                 t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32,
+                                 screen_resolves(t, K) ? kTieWindow : 0.f};
   if (t.geo == kGeoAnnular11) {
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (K <= 2) return screen::launch_angles<AnnularCounts11, 2, RSC_FP16>(t, prm, st);

@@ -103,8 +103,10 @@ int launch_dict_tables(const DictBuild& p, void* stream);
 
 // Kernel launchers.  Return a hipError_t as int.
 int launch_project(const DeviceTables& t, const float* patches, int64_t P, float* xhat, void* stream);
+// marked: only the patches whose first atom the screened encoder left at kTieMark.
+constexpr int kTieMark = -2;
 int launch_encode(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
-                  int32_t* angle, float* coef, float* resid2, void* stream);
+                  int32_t* angle, float* coef, float* resid2, void* stream, bool marked = false);
 int launch_synthesize(const DeviceTables& t, const int32_t* atom, const int32_t* angle_idx,
                       const float* theta, const float* weight, int64_t P, int J,
                       const float* noise, float* out, void* stream);
@@ -116,7 +118,7 @@ bool encode_supported_geo(const DeviceTables& t);   // the encoder is compiled f
 // R <= 64, K <= 4.
 constexpr int kAnnularMaxK = 4, kAnnularMaxR = 64;
 int launch_encode_annular(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom,
-                          int32_t* angle, float* coef, float* resid2, void* stream);
+                          int32_t* angle, float* coef, float* resid2, void* stream, bool marked);
 size_t encode_lds_bytes(const DeviceTables& t, int tile);
 // 16x16 FP32 tile: LDS of one block with (irows) or without the i * dictionary copy, whether
 // the copy is used (both tables fit a CU), and the block size of a launch over wave_tiles
@@ -169,6 +171,8 @@ int screen_waves(const DeviceTables& t, int kmax);
 double screen_mfma_flops_per_patch(const DeviceTables& t, int K);
 int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
                          float* coef, float* resid2, void* stream);
+// Whether ties of the screened FP32 pursuit are resolved by the full FP32 form (rsc_encode_screen.hip).
+bool screen_resolves(const DeviceTables& t, int K);
 size_t images_workspace_bytes(int n_images);
 // rsc_project_images_noalloc: the plan in a static device array of this many images.
 constexpr int kNoAllocMaxImages = 65535;
