@@ -229,8 +229,8 @@ rsc_status rsc_encode_info(const rsc_handle* h, int K, int* tile, double* mfma_f
 rsc_status rsc_get_launch(const rsc_handle* h, int* tile, int* blocks_per_cu);
 
 /*
- * Autotuner: times rsc_omp_encode on a representative sample for every usable tile
- * shape and blocks_per_cu = 1..4 (median of reps runs, HIP events on the stream),
+ * Autotuner: times rsc_omp_encode on a representative sample for every usable form (the
+ * screened one in place of RSC_TILE_16 where there is one) and blocks_per_cu = 1..4 (median of reps runs, HIP events on the stream),
  * then keeps the fastest in the handle.  Blocking; not for a hot loop.
  *   xhat              device [P, B] sample, P >= 1
  *   atom, angle, coef device [P, K] scratch outputs (overwritten)
@@ -288,7 +288,10 @@ rsc_status rsc_encode_workspace_size(const rsc_handle* h, int64_t P, int K, size
  * a score, so the atom with the exact maximum is always among them) is re-scored over
  * all angles in FP32, and the selection is taken from the FP32 scores.  So the screen only
  * leaves out atoms that cannot win, and the selection is that of FP32 scores of every atom; the
- * least squares, the residual and the outputs are FP32 as in the other forms.  BF16 handles
+ * least squares, the residual and the outputs are FP32 as in the other forms.  On FP32 handles
+ * with M K >= 128, a patch with a selection that another atom or angle misses by less than 2^-22
+ * ||residual||, which the order of the FP32 sums decides, is coded by the full form (the tile that
+ * RSC_TILE_AUTO takes where there is no screen) in a second launch.  BF16 handles
  * re-score the atom with the largest 16-bit maximum first and then only the candidates
  * whose 16-bit maximum reaches its FP32 maximum minus 4.25u ||residual|| (the atom with
  * the largest FP32 maximum always does).
@@ -577,7 +580,8 @@ rsc_status rsc_synthesize_hat(const rsc_handle* h, const float* xhat, int64_t P,
  *   out[0]  pursuit steps (patch x step) that re-scored candidates (16-bit handles; else 0)
  *   out[1]  candidates re-scored in FP32, summed over those steps (16-bit handles; else 0)
  *   out[2]  largest number of candidates in one step (16-bit handles; else 0)
- *   out[3]  steps whose least squares went to the FP64 solve (every handle)
+ *   out[3]  steps whose least squares went to the FP64 solve (every handle; a tied patch of an
+ *           FP32 handle is coded by two launches, and both count)
  *   out     host [4] int64, or NULL; reset != 0 clears the counters after reading.
  * Blocking: waits for the whole device first.  Launches that overlap the call may
  * or may not be counted.
