@@ -289,7 +289,7 @@ rsc_status rsc_encode_workspace_size(const rsc_handle* h, int64_t P, int K, size
  * all angles in FP32, and the selection is taken from the FP32 scores.  So the screen only
  * leaves out atoms that cannot win, and the selection is that of FP32 scores of every atom; the
  * least squares, the residual and the outputs are FP32 as in the other forms.  On FP32 handles
- * with M K >= 128, a patch with a selection that another atom or angle misses by less than 2^-22
+ * with M K >= 64, a patch with a selection that another atom or angle misses by less than 2^-22
  * ||residual||, which the order of the FP32 sums decides, is coded by the full form (the tile that
  * RSC_TILE_AUTO takes where there is no screen) in a second launch.  BF16 handles
  * re-score the atom with the largest 16-bit maximum first and then only the candidates

@@ -49,13 +49,21 @@ using enc::write_codes;
 
 // ============================================================== 32x32 tiles
 // F[q]: stage-2 operand of harmonic q for angle rows r < R/2 (rows past R/2 zero).
-template <int S, int T, int KMAX>
+// MARKED: as in encode16_kernel.
+template <int S, int T, int KMAX, bool MARKED>
 __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int NG) {
   using L = Layout<S, T, 2>;
   constexpr int NKS = L::NKS, NQ = L::NQ, B = L::B;
   extern __shared__ float lds[];
   const int R = prm.R, M = prm.M, K = prm.K, HALF = prm.R / 2;
-  if (prm.marked && !enc::block_has_mark<32>(prm, 4)) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t few = prm.P;                   // coop: as in encode16_kernel
+  bool coop = false;
+  if constexpr (MARKED) {
+    const int n = enc::block_marks<32>(prm, 4, lane, lds, few);
+    if (n == 0) return;
+    coop = prm.xch > 0 && n <= 32;
+  }
   float* sA = lds;                       // [NG][NKS][64]
   float* sHat = sA + NG * NKS * 64;      // [NG*16][B]
   float* sCs = sHat + NG * 16 * B;       // [2][NQ][R]
@@ -67,7 +75,6 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
   }
   __syncthreads();
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 31, u = lane >> 5;
   const LsTables tb{prm.gramH, prm.gramH64, prm.cs64, prm.xhat, M, R, kCondMaxFp32};
   unsigned n64 = 0;
@@ -75,8 +82,9 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
 #pragma unroll
   for (int q = 0; q < NQ; ++q) F[q] = prm.dftA[q * 64 + lane];
 
-  enc::WavePatches<32> tiles(prm, 4, wave);
-  for (int64_t p; tiles.next(lane, p);) {
+  enc::WavePatches<32, MARKED> tiles(prm, 4, wave);
+  bool first = true;
+  for (int64_t p = few; MARKED && coop ? first : tiles.next(lane, p); first = false) {
     const bool valid = p < prm.P;
     float res[NKS];
     static_for<NKS>([&](auto J) {
@@ -97,7 +105,8 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
       // ---------------- (b) pass 1: best atom by its maximum over all angles
       float best = -1.f;
       int bm = 0;
-      for (int g = 0; g < NG; ++g) {
+      const int g0 = MARKED && coop ? wave : 0, gs = MARKED && coop ? 4 : 1;
+      for (int g = g0; g < NG; g += gs) {
         const float* Ag = sA + g * NKS * 64 + lane;
         f32x16 acc[NQ];
 #pragma unroll
@@ -168,6 +177,7 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
         }
         bm = upd ? g * 16 + ba : bm;
       }
+      if (MARKED && coop) enc::block_best<32>(lds + prm.xch, 4, wave, lane, best, bm);
       // ---------------- (b) pass 2: angles of the best atom, its stage-2 operand formed
       // again from its dictionary row (no per-atom copy is kept in pass 1)
       int rs;
@@ -212,7 +222,8 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
       n64 += (ls_update<L, KMAX>(st, ls, it, bm, rs, cval, sHat, sCs, tb, p, u, res) && u == 0) ? 1u : 0u;
     }
     const float rn2 = norm2<L>(res);
-    if (valid && u == 0) write_codes<L, KMAX>(prm, p, st, rn2);
+    if (MARKED && coop && wave > 0) n64 = 0;
+    if (valid && u == 0 && !(MARKED && coop && wave > 0)) write_codes<L, KMAX>(prm, p, st, rn2);
   }
   count_fp64(prm.stats, n64, lane);
 }
@@ -220,18 +231,28 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
 // ============================================================== launchers
 template <int S, int T, int KMAX>
 int launch32(const DeviceTables& t, const EncodeParams& prm, hipStream_t st) {
-  return launch_persistent(encode32_kernel<S, T, KMAX>, encode_lds_bytes(t, RSC_TILE_32), (prm.P + 31) / 32,
-                           t.enc_bpc, st, prm, t.NG);
+  size_t lds = encode_lds_bytes(t, RSC_TILE_32);
+  const EncodeParams q = enc::with_exchange(prm, lds);
+  return launch_persistent(prm.marked ? encode32_kernel<S, T, KMAX, true> : encode32_kernel<S, T, KMAX, false>, lds,
+                           (prm.P + 31) / 32, t.enc_bpc, st, q, t.NG);
 }
 
 template <class C, int HT, int KMAX, bool SPLIT>
 int launch16(const DeviceTables& t, const EncodeParams& prm, hipStream_t st) {
   const int64_t tiles = (prm.P + 15) / 16;
-  if (encode16_irows(t))
-    return launch_persistent_n(encode16_kernel<C, HT, KMAX, SPLIT, true>, encode16_threads(tiles),
-                               encode16_lds_bytes(t, true), tiles, t.enc_bpc, st, prm);
-  return launch_persistent(encode16_kernel<C, HT, KMAX, SPLIT, false>, encode16_lds_bytes(t, false), tiles,
-                           t.enc_bpc, st, prm);
+  const bool irows = encode16_irows(t);
+  size_t lds = encode16_lds_bytes(t, irows);
+  const EncodeParams q = enc::with_exchange(prm, lds);
+  const int threads = irows ? encode16_threads(tiles) : 256;
+  auto run = [&](auto kern) { return launch_persistent_n(kern, threads, lds, tiles, t.enc_bpc, st, q); };
+  // the screened encoder has R <= 64: at most two angle tiles with the split, four without
+  if constexpr (HT <= (SPLIT ? 2 : 4))
+    if (prm.marked)
+      return irows ? run(encode16_kernel<C, HT, KMAX, SPLIT, true, true>)
+                   : run(encode16_kernel<C, HT, KMAX, SPLIT, false, true>);
+  if (prm.marked) return int(hipErrorInvalidValue);
+  return irows ? run(encode16_kernel<C, HT, KMAX, SPLIT, true, false>)
+               : run(encode16_kernel<C, HT, KMAX, SPLIT, false, false>);
 }
 
 template <class C, int HT, bool SPLIT>

@@ -10,6 +10,8 @@
 // steer each harmonic block by its own count.  Compiled for even R <= 64 and K <= 4.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "rsc_device.h"
 #include "rsc_encode16.h"
 #include "rsc_internal.h"
@@ -21,11 +23,18 @@ namespace {
 template <class C, int HT, int KMAX>
 int launchA(const DeviceTables& t, const enc::EncodeParams& prm, hipStream_t st) {
   const int64_t tiles = (prm.P + 15) / 16;
-  if (encode16_irows(t))
-    return launch_persistent_n(enc::encode16_kernel<C, HT, KMAX, true, true>, encode16_threads(tiles),
-                               encode16_lds_bytes(t, true), tiles, t.enc_bpc, st, prm);
-  return launch_persistent(enc::encode16_kernel<C, HT, KMAX, true, false>, encode16_lds_bytes(t, false), tiles,
-                           t.enc_bpc, st, prm);
+  const bool irows = encode16_irows(t);
+  size_t lds = encode16_lds_bytes(t, irows);
+  const enc::EncodeParams q = enc::with_exchange(prm, lds);
+  const int threads = irows ? encode16_threads(tiles) : 256;
+  auto run = [&](auto kern) { return launch_persistent_n(kern, threads, lds, tiles, t.enc_bpc, st, q); };
+  if constexpr (std::is_same_v<C, AnnularCounts11>)
+    if (prm.marked)
+      return irows ? run(enc::encode16_kernel<C, HT, KMAX, true, true, true>)
+                   : run(enc::encode16_kernel<C, HT, KMAX, true, false, true>);
+  if (prm.marked) return int(hipErrorInvalidValue);
+  return irows ? run(enc::encode16_kernel<C, HT, KMAX, true, true, false>)
+               : run(enc::encode16_kernel<C, HT, KMAX, true, false, false>);
 }
 
 template <class C>

@@ -13,7 +13,7 @@ namespace {
 int kmax_of(const DeviceTables& t, int K) {
   if (t.scrPrec == RSC_BF16) return t.T == 5 ? (K <= 4 ? 4 : 8) : (K <= 6 ? 6 : 8);
   if (K <= 4) return K <= 2 ? 2 : 4;
-  return t.T == 7 && K <= 6 ? 6 : 8;
+  return K <= 6 ? 6 : 8;
 }
 
 size_t table_bytes(const DeviceTables& t) {
@@ -31,10 +31,10 @@ size_t table_bytes(const DeviceTables& t) {
 // windows none differed any more, where without it about 130 do; the gaps that flip are of the
 // size of the summation error, about 0.3 of that.
 // The second launch costs about 3 us where nothing is marked and the latency of one tile's pursuit
-// (100 us, 240 us at 15x15 with 6 steps) where something is, so it is left out where the ties are
-// rare: for M K below 128 (one atom of a class dictionary, or the few atoms of a small call).
+// (50 to 130 us) where something is, so it is left out where the ties are rarest and the calls
+// shortest: for M K below 64 (2,000 patches, 16 atoms, 2 steps: 22 us with one launch, 25 with two).
 constexpr float kTieWindow = 0x1p-22f;
-constexpr int kTieWork = 128;
+constexpr int kTieWork = 64;
 
 }  // namespace
 
@@ -68,14 +68,14 @@ double screen_mfma_flops_per_patch(const DeviceTables& t, int K) {
 }
 
 int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                         float* coef, float* resid2, void* stream) {
+                         float* coef, float* resid2, void* stream, bool mark) {
   if (P <= 0) return 0;
   const screen::ScreenParams prm{xhat, P, K, t.M, t.R,
                                  reinterpret_cast<const uint4*>(t.lpA), t.dictPairs, t.dictHat,
                                  reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.norm2, t.gramH64, t.cs64,
                                  atom, angle, coef, resid2, t.lpStats,
                                  t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32,
-                                 screen_resolves(t, K) ? kTieWindow : 0.f};
+                                 mark ? kTieWindow : 0.f};
   if (t.geo == kGeoAnnular11) {
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (K <= 2) return screen::launch_angles<AnnularCounts11, 2, RSC_FP16>(t, prm, st);
