@@ -3,7 +3,8 @@
 //
 // The per-class pursuits are the library's encoder, one launch per class dictionary;
 // this file holds what follows them:
-//   * classify_min_kernel: after class c's pursuit, a patch keeps the smaller of its
+//   * classify_min_kernel: after class c's pursuit (where the encoder does not do it itself,
+//     rsc_encode_screen.h), a patch keeps the smaller of its
 //     running error and class c's (strictly smaller replaces, so ties stay with the
 //     smaller class index);
 //   * label_hist_kernel: one block per group of consecutive patches (an image's

@@ -73,6 +73,9 @@ struct ScreenParams {
   float cond_max;              // least squares in FP64 beyond this bound (ls_update)
   bool count;                  // whether candidates are counted (16-bit handles)
   float tie;                   // > 0: patches with a selection decided by less than tie ||r|| get kTieMark
+  int32_t* label;              // not null: no codes; each patch keeps the smaller of sse and its squared
+  float* sse;                  // residual norm, and class cls with it where that is the smaller (class 0
+  int cls;                     // always), as classify_min_kernel
 };
 
 // The least-squares state of the wave's 32 patches in LDS: float4 q of patch col at
@@ -733,7 +736,12 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
                                  reinterpret_cast<float*>(sState), res) ? 1 : 0;
     }
     const float rn2 = norm2<L>(res);
-    if (valid && u == 0) {
+    if (prm.label) {
+      if (valid && u == 0 && (prm.cls == 0 || rn2 < prm.sse[p])) {
+        prm.sse[p] = rn2;
+        prm.label[p] = prm.cls;
+      }
+    } else if (valid && u == 0) {
 #pragma unroll
       for (int i = 0; i < KMAX; ++i) {
         if (i < K) {

@@ -68,14 +68,14 @@ double screen_mfma_flops_per_patch(const DeviceTables& t, int K) {
 }
 
 int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                         float* coef, float* resid2, void* stream, bool mark) {
+                         float* coef, float* resid2, void* stream, bool mark, ClassOut cls) {
   if (P <= 0) return 0;
   const screen::ScreenParams prm{xhat, P, K, t.M, t.R,
                                  reinterpret_cast<const uint4*>(t.lpA), t.dictPairs, t.dictHat,
                                  reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.norm2, t.gramH64, t.cs64,
                                  atom, angle, coef, resid2, t.lpStats,
                                  t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32,
-                                 mark ? kTieWindow : 0.f};
+                                 mark ? kTieWindow : 0.f, cls.label, cls.sse, cls.c};
   if (t.geo == kGeoAnnular11) {
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (K <= 2) return screen::launch_angles<AnnularCounts11, 2, RSC_FP16>(t, prm, st);

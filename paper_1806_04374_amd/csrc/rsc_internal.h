@@ -169,9 +169,16 @@ bool screen_usable(const DeviceTables& t, int K);
 size_t screen_lds_bytes(const DeviceTables& t, int kmax, int waves);
 int screen_waves(const DeviceTables& t, int kmax);
 double screen_mfma_flops_per_patch(const DeviceTables& t, int K);
-// mark: patches with a near tie are left with kTieMark for a marked launch_encode.
+// mark: patches with a near tie are left with kTieMark for a marked launch_encode.  With cls.label the
+// codes (which may then be null) are not written: the patches' labels and errors take class cls.c in,
+// as by launch_classify_min after it.
+struct ClassOut {
+  int32_t* label = nullptr;
+  float* sse = nullptr;
+  int c = 0;
+};
 int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                         float* coef, float* resid2, void* stream, bool mark);
+                         float* coef, float* resid2, void* stream, bool mark, ClassOut cls = {});
 // Whether ties of the screened FP32 pursuit are resolved by the full FP32 form (rsc_encode_screen.hip).
 bool screen_resolves(const DeviceTables& t, int K);
 size_t images_workspace_bytes(int n_images);

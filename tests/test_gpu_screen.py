@@ -156,3 +156,26 @@ def test_autotune_refuses_annular_beyond_four(dev):
     x = torch.randn((100, h.B), device=dev)
     with pytest.raises(rsc.RscError):
         rsc.rsc_autotune_encode(h, x, 5)
+
+
+@pytest.mark.parametrize("kind,N,K,P", [("grid", 15, 1, 1), ("grid", 15, 2, 33), ("grid", 11, 1, 5003), ("annular", 11, 1, 700)])
+def test_classify_takes_the_smallest_error(dev, kind, N, K, P):
+    """Labels and errors that the screened encoder writes itself are those of one pursuit per class:
+    the smallest squared residual norm, the first class on equal ones (the first two share a
+    dictionary), bit for bit (M K < 64: the same launches)."""
+    from paper_1806_04374_amd import rsc
+    basis, _ = _make(kind, N)
+    rng = np.random.default_rng([N, K, P])
+    hs = []
+    for c in range(4):
+        if c != 1:
+            d = rng.standard_normal((20 + c, basis.B)).astype(np.float32)
+        h = _make(kind, N)[1] if c < 3 or kind == "annular" else rsc.rsc_create(N, basis.S, basis.T, prec="bf16")
+        rsc.rsc_set_dictionary(h, d / np.linalg.norm(d, axis=1, keepdims=True), 48)
+        hs.append(h)
+    x = torch.randn((P, basis.B), generator=torch.Generator(device=dev).manual_seed(P), device=dev)
+    label, sse = rsc.rsc_classify(hs, x, K)
+    r2 = torch.stack([rsc.rsc_omp_encode(h, x, K)[3].clone() for h in hs])
+    want, at = r2.min(0)
+    at = (r2 == want).to(torch.int32).argmax(0)
+    assert torch.equal(sse, want) and torch.equal(label.long(), at.long())
