@@ -167,15 +167,26 @@ struct RowBatches {
   // index of harmonic k's first pair within the row's pairs, and the floats before the pairs
   __host__ __device__ static constexpr int pair0(int k) { return (L::base(k) - L::Sk(0)) / 2; }
   static constexpr int S0 = 2 * L::J0;
-  // f(k, i, (Re, Im)) for every profile i of every harmonic k >= 1, g(k) after each harmonic
-  template <class F, class G>
-  __device__ __forceinline__ static void each(const float* __restrict__ row, F f, G g) {
-    const float2* pr = reinterpret_cast<const float2*>(row + S0);
-    float2 buf[2][kRowPairs];
+  // f(k, i, x, y) for every profile i of every harmonic k >= 1, g(k) after each harmonic.  (x, y):
+  // the pair (Re, Im), one 8-byte read; with OWN the part that the lane's half-wave holds (u = 0:
+  // Re, 1: Im) and the other one
+  template <bool OWN, class F, class G>
+  __device__ __forceinline__ static void each(const float* __restrict__ row, int u, F f, G g) {
+    const float *px = row + S0 + (OWN ? u : 0), *py = row + S0 + (OWN ? 1 - u : 1);
+    float x[2][kRowPairs], y[2][kRowPairs];
     auto fetch = [&](auto B1) {
       constexpr int b = decltype(B1)::value, lo = pair0(first(b)), hi = pair0(first(b + 1) <= L::T ? first(b + 1) : L::T + 1);
 #pragma unroll
-      for (int i = lo; i < hi; ++i) buf[b % 2][i - lo] = pr[i];
+      for (int i = lo; i < hi; ++i) {
+        if constexpr (OWN) {
+          x[b % 2][i - lo] = px[2 * i];
+          y[b % 2][i - lo] = py[2 * i];
+        } else {
+          const float2 d = reinterpret_cast<const float2*>(px)[i];
+          x[b % 2][i - lo] = d.x;
+          y[b % 2][i - lo] = d.y;
+        }
+      }
     };
     fetch(std::integral_constant<int, 0>{});
     static_for<count()>([&](auto B1) {
@@ -185,8 +196,8 @@ struct RowBatches {
       static_for<k1 - k0>([&](auto K1) {
         constexpr int k = k0 + decltype(K1)::value;
         static_for<L::Sk(k)>([&](auto I) {
-          constexpr int i = decltype(I)::value;
-          f(std::integral_constant<int, k>{}, std::integral_constant<int, i>{}, buf[b % 2][pair0(k) - pair0(k0) + i]);
+          constexpr int i = decltype(I)::value, j = pair0(k) - pair0(k0) + i;
+          f(std::integral_constant<int, k>{}, std::integral_constant<int, i>{}, x[b % 2][j], y[b % 2][j]);
         });
         g(std::integral_constant<int, k>{});
       });
@@ -208,10 +219,10 @@ __device__ __forceinline__ void row_operand(const float* __restrict__ row, int u
   float pr[L::NQ], pi[L::NQ];
   zero(pr);
   zero(pi);
-  RowBatches<L>::each(row, [&](auto K1, auto I, float2 d) {
+  RowBatches<L>::template each<false>(row, u, [&](auto K1, auto I, float re, float im) {
     constexpr int k = decltype(K1)::value, j = L::joff(k) + decltype(I)::value;
-    pr[k] = fmaf(d.x, res[j], pr[k]);
-    pi[k] = fmaf(d.y, res[j], pi[k]);
+    pr[k] = fmaf(re, res[j], pr[k]);
+    pi[k] = fmaf(im, res[j], pi[k]);
   }, [&](auto K1) {
     // low (Re x): Re += dRe x, Im -= dIm x; high (Im x): Re += dIm x, Im += dRe x
     constexpr int k = decltype(K1)::value;
@@ -228,8 +239,11 @@ __device__ __forceinline__ void row_operand(const float* __restrict__ row, int u
 }
 
 // acc += alpha S_r d for the atom in `row` on this lane's coordinates; cs: (cos, sin) of this
-// angle per harmonic.  Re' = c Re + s Im, Im' = c Im - s Re: the two factors of a harmonic's
-// (Re, Im) pair are picked per lane once, so a coordinate costs two fused multiply-adds.
+// angle per harmonic.  Re' = c Re + s Im, Im' = c Im - s Re: the product with the other part of a
+// pair is added first and the one with the lane's own part last, as in steer_axpy, so that the
+// residual is rounded as there (Re first in both half-waves saves the half-waves' own addresses
+// and nothing measurable: 0 to 1% of an encode; reading the pairs whole and selecting the parts
+// costs 1 to 3%).
 template <class L>
 __device__ __forceinline__ void row_axpy(float (&acc)[L::NKS], float alpha, const float* __restrict__ row,
                                          const float2* __restrict__ cs, int u) {
@@ -239,15 +253,14 @@ __device__ __forceinline__ void row_axpy(float (&acc)[L::NKS], float alpha, cons
   float2 w[L::NQ];
 #pragma unroll
   for (int k = 1; k < L::NQ; ++k) w[k] = cs[k];
-  float fx = 0.f, fy = 0.f;
-  RowBatches<L>::each(row, [&](auto K1, auto I, float2 d) {
+  float c = 0.f, s = 0.f;
+  RowBatches<L>::template each<true>(row, u, [&](auto K1, auto I, float own, float oth) {
     constexpr int k = decltype(K1)::value, i = decltype(I)::value, j = L::joff(k) + i;
     if constexpr (i == 0) {
-      const float c = alpha * w[k].x, s = alpha * w[k].y;
-      fx = u ? -s : c;
-      fy = u ? c : s;
+      c = alpha * w[k].x;
+      s = (u ? -alpha : alpha) * w[k].y;
     }
-    acc[j] = fmaf(d.x, fx, fmaf(d.y, fy, acc[j]));
+    acc[j] = fmaf(own, c, fmaf(oth, s, acc[j]));
   }, [](auto) {});
 #pragma unroll
   for (int j = 0; j < L::J0; ++j) acc[j] = fmaf(alpha, d0[j], acc[j]);
