@@ -59,17 +59,21 @@ typedef enum {
 } rsc_status;
 
 typedef enum {
-  RSC_FP32 = 0,            /* projection, selection and least squares in FP32 */
+  RSC_FP32 = 0,            /* projection, scores and least squares in FP32; under RSC_TILE_AUTO
+                              atoms that cannot win a step are left out by an FP16 screen with a
+                              proven bound (see rsc_omp_encode) */
   RSC_BF16 = 1,            /* correlation operands in BF16, FP32 accumulation, FP32 re-score */
   RSC_FP16 = 2             /* correlation operands in FP16, FP32 accumulation, FP32 re-score */
 } rsc_precision;
 
-/* Form of the FP32 encoder (all give identical codes up to FP32 rounding order). */
+/* Form of the FP32 encoder.  RSC_TILE_16 and RSC_TILE_32 give identical codes up to FP32 rounding
+   order; RSC_TILE_AUTO gives the codes of one of them, bit for bit. */
 typedef enum {
   RSC_TILE_AUTO = 0,       /* the library's choice: the screened form (see rsc_omp_encode) for
                               the 11x11 and 15x15 grids and the annular basis at N = 11 with
-                              M <= 128 and R <= 64 where its tables fit a CU's LDS; else
-                              RSC_TILE_32 where it is compiled and R > 32, else RSC_TILE_16 */
+                              M <= 128 and R <= 64 where its tables fit a CU's LDS.  Its codes are
+                              those of RSC_TILE_32 where that is compiled and R > 32, else
+                              of RSC_TILE_16; that form itself runs everywhere else */
   RSC_TILE_16 = 1,         /* 16 patches x 8 atoms per MFMA tile (v_mfma_f32_16x16x4f32) */
   RSC_TILE_32 = 2          /* 32 patches x 16 atoms per MFMA tile (v_mfma_f32_32x32x2f32);
                               S = T = 5, K <= 4 and R <= 64 only */
@@ -230,7 +234,8 @@ rsc_status rsc_get_launch(const rsc_handle* h, int* tile, int* blocks_per_cu);
 
 /*
  * Autotuner: times rsc_omp_encode on a representative sample for every usable form (the
- * screened one in place of RSC_TILE_16 where there is one) and blocks_per_cu = 1..4 (median of reps runs, HIP events on the stream),
+ * screened one in place of RSC_TILE_16 where there is one) and blocks_per_cu = 1..4 (median of
+ * reps runs, HIP events on the stream),
  * then keeps the fastest in the handle.  Blocking; not for a hot loop.
  *   xhat              device [P, B] sample, P >= 1
  *   atom, angle, coef device [P, K] scratch outputs (overwritten)
@@ -289,9 +294,9 @@ rsc_status rsc_encode_workspace_size(const rsc_handle* h, int64_t P, int K, size
  * all angles in FP32, and the selection is taken from the FP32 scores.  So the screen only
  * leaves out atoms that cannot win, and the selection is that of FP32 scores of every atom; the
  * least squares, the residual and the outputs are FP32 as in the other forms.  On FP32 handles
- * with M K >= 64, a patch with a selection that another atom or angle misses by less than 2^-22
- * ||residual||, which the order of the FP32 sums decides, is coded by the full form (the tile that
- * RSC_TILE_AUTO takes where there is no screen) in a second launch.  BF16 handles
+ * every sum is formed in the order of the tile that RSC_TILE_AUTO takes where there is no screen,
+ * and atoms within that order's rounding of one another are compared as that tile compares
+ * them, so all outputs are that tile's, bit for bit.  BF16 handles
  * re-score the atom with the largest 16-bit maximum first and then only the candidates
  * whose 16-bit maximum reaches its FP32 maximum minus 4.25u ||residual|| (the atom with
  * the largest FP32 maximum always does).
@@ -580,8 +585,7 @@ rsc_status rsc_synthesize_hat(const rsc_handle* h, const float* xhat, int64_t P,
  *   out[0]  pursuit steps (patch x step) that re-scored candidates (16-bit handles; else 0)
  *   out[1]  candidates re-scored in FP32, summed over those steps (16-bit handles; else 0)
  *   out[2]  largest number of candidates in one step (16-bit handles; else 0)
- *   out[3]  steps whose least squares went to the FP64 solve (every handle; a tied patch of an
- *           FP32 handle is coded by two launches, and both count)
+ *   out[3]  steps whose least squares went to the FP64 solve (every handle)
  *   out     host [4] int64, or NULL; reset != 0 clears the counters after reading.
  * Blocking: waits for the whole device first.  Launches that overlap the call may
  * or may not be counted.

@@ -707,9 +707,10 @@ rsc_status rsc_set_dictionary(rsc_handle* h, const float* d_hat, int M, int R, v
             lpF16[((size_t(o) * RT + t) * 64 + l) * 8 + i] = cvt(v);
           }
         }
-    // FP32 angle DFT operand: radix-2 split (rows r < R/2) for even R in 33..64, else
-    // RT tiles of the direct DFT; contraction lanes (cos, -sin), (1, 0) for k = 0
-    split = R % 2 == 0 && R > 32;
+    // FP32 angle DFT operand: radix-2 split (rows r < R/2) for even R, as in the full form (16-bit
+    // handles: even R > 32), else RT tiles of the direct DFT; contraction lanes (cos, -sin), (1, 0)
+    // for k = 0
+    split = R % 2 == 0 && (R > 32 || !lp);
     const int FT = split ? 1 : RT, rows = split ? R / 2 : R;
     lpF32.assign(size_t(FT) * NQ * 64, 0.f);
     for (int t = 0; t < FT; ++t)
@@ -838,14 +839,12 @@ int encoder_tile(const rsc_handle* h, rsc_tile tile, int K) {
   return want32 && rsc::tile32_usable(h->dev, K) ? RSC_TILE_32 : RSC_TILE_16;
 }
 
-// The screened encoder, and for FP32 handles the full one over the patches that it marked: those
-// with a selection that FP32 rounding decides.
+// The screened encoder; its codes on an FP32 handle are those of the tile that RSC_TILE_AUTO takes
+// where there is no screen.
 int encode_screened(const rsc_handle* h, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                    float* coef, float* resid2, void* stream) {
-  const bool mark = rsc::screen_resolves(h->dev, K);
-  const int e = rsc::launch_encode_screen(h->dev, xhat, P, K, atom, angle, coef, resid2, stream, mark);
-  if (e || !mark) return e;
-  return rsc::launch_encode(h->dev, encoder_tile(h, RSC_TILE_AUTO, K), xhat, P, K, atom, angle, coef, resid2, stream, true);
+                    float* coef, float* resid2, void* stream, rsc::ClassOut cls = {}) {
+  return rsc::launch_encode_screen(h->dev, encoder_tile(h, RSC_TILE_AUTO, K), xhat, P, K, atom, angle, coef, resid2,
+                                   stream, cls);
 }
 
 rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int K, int32_t* atom,
@@ -1223,14 +1222,12 @@ rsc_status rsc_classify(const rsc_handle* const* classes, int C, const float* xh
   float* coef = reinterpret_cast<float*>(w + L.coef);
   float* r2 = reinterpret_cast<float*>(w + L.resid);
   for (int c = 0; c < C; ++c) {
-    // the screened encoder takes the class in by itself where no tie launch follows: with K = 1 only
-    // the error matters, and two atoms that tie leave the same one (161,000 windows, 24 classes of
-    // 100 atoms: 1.96 -> 1.88 ms, codes and a launch over the errors per class left out)
-    if (encoder_screened(classes[c], K) && (K == 1 || !rsc::screen_resolves(classes[c]->dev, K))) {
+    // the screened encoder takes the class in by itself (161,000 windows, 24 classes of 100 atoms:
+    // 1.96 -> 1.88 ms, codes and a launch over the errors per class left out)
+    if (encoder_screened(classes[c], K)) {
       if (rsc_status f = check_fault(classes[c])) return f;
       const rsc_status s = dict_launch(classes[c], stream, "encode launch", [&] {
-        return rsc::launch_encode_screen(classes[c]->dev, xhat, P, K, nullptr, nullptr, nullptr, nullptr, stream, false,
-                                         {label, sse, c});
+        return encode_screened(classes[c], xhat, P, K, nullptr, nullptr, nullptr, nullptr, stream, {label, sse, c});
       });
       if (s != RSC_OK) return s;
       continue;

@@ -387,8 +387,11 @@ __device__ __forceinline__ double patch_sum64(double x) {
 // ends the pursuit); then the coefficients, the selection and the residual
 // x_hat - sum_i a_i column_i are replaced.  The factor and the solution live in
 // dynamically indexed local arrays (private memory): the path is rare, and its loops
-// indexed at run time keep the factor out of the registers of the pursuit's main path.
-template <class L, int KMAX>
+// indexed at run time keep the factor out of the registers of the pursuit's main path.  ORD: the
+// lanes whose order the inner products are summed in; ORD = 4 in a two-lane layout sums the even
+// and the odd profiles (registers of a harmonic) apart, which is what lanes 0, 1 and 2, 3 of
+// the four-lane layout hold.
+template <class L, int KMAX, int ORD = L::W>
 __device__ __forceinline__ bool ls_solve64(PursuitState<KMAX>& st, int it, int ms, int rs, bool go,
                                                      const float* hat, const LsTables& tb, int64_t p, int u,
                                                      float (&res)[L::NKS]) {
@@ -421,14 +424,23 @@ __device__ __forceinline__ bool ls_solve64(PursuitState<KMAX>& st, int it, int m
   const int64_t pp = good ? p : 0;
 #pragma unroll 1
   for (int i = 0; i <= it; ++i) {
-    double b = 0.0;
+    double b = 0.0, b2 = 0.0;
 #pragma unroll 1
     for (int j = 0; j < L::NKS; ++j) {
       const int c = L::coord(j, u);
       const double x = (good && c >= 0) ? double(tb.xhat[pp * L::B + c]) : 0.0;
-      b += steer64<L>(hat, tb.cs64, R, cm[i], cr[i], j, u) * x;
+      if constexpr (ORD == L::W) {
+        b += steer64<L>(hat, tb.cs64, R, cm[i], cr[i], j, u) * x;
+      } else {
+        const bool odd = L::pair(j) & 1;
+        double s = odd ? b2 : b;
+        s += steer64<L>(hat, tb.cs64, R, cm[i], cr[i], j, u) * x;
+        b = odd ? b : s;
+        b2 = odd ? s : b2;
+      }
     }
     b = patch_sum64<L::W>(b);
+    if constexpr (ORD != L::W) b += patch_sum64<L::W>(b2);
 #pragma unroll 1
     for (int l = 0; l < i; ++l) b -= Lc[i][l] * y[l];
     y[i] = b / Lc[i][i];
@@ -584,12 +596,26 @@ __device__ __forceinline__ bool ls_update(PursuitState<KMAX>& st, LsState<KMAX>&
   return go64;
 }
 
-template <class L>
+// Squared norm over a patch, summed as W lanes do: each lane one chain over its registers, then
+// the lanes.  With W = 4 in a two-lane layout, the even profiles (registers of a harmonic) are the
+// four-lane layout's lanes 0 and 1, the odd ones lanes 2 and 3, so the sum has the same bits in
+// both.  The order is written out because results depend on it: the four-lane chain of the
+// 11x11 grid takes profile 4 of harmonic 0 before profile 0, as its residual norms always have.
+template <class L, int W = L::W>
 __device__ __forceinline__ float norm2(const float (&v)[L::NKS]) {
-  float a = 0.f;
+  constexpr int NC = W / L::W;                       // chains per lane
+  constexpr bool second_first = W == 4 && L::T == 5;
+  float a[NC];
 #pragma unroll
-  for (int j = 0; j < L::NKS; ++j) a += v[j] * v[j];
-  return patch_sum<L::W>(a);
+  for (int c = 0; c < NC; ++c) a[c] = 0.f;
+  if constexpr (second_first) a[0] = v[NC] * v[NC];
+  static_for<L::NKS>([&](auto J) {
+    constexpr int j = decltype(J)::value, c = L::pair(j) % NC;
+    if constexpr (!(second_first && j == NC)) a[c] = fmaf(v[j], v[j], a[c]);
+  });
+  float n = patch_sum<L::W>(a[0]);
+  if constexpr (NC == 2) n += patch_sum<L::W>(a[1]);
+  return n;
 }
 
 }  // namespace rsc

@@ -49,21 +49,12 @@ using enc::write_codes;
 
 // ============================================================== 32x32 tiles
 // F[q]: stage-2 operand of harmonic q for angle rows r < R/2 (rows past R/2 zero).
-// MARKED: as in encode16_kernel.
-template <int S, int T, int KMAX, bool MARKED>
+template <int S, int T, int KMAX>
 __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int NG) {
   using L = Layout<S, T, 2>;
   constexpr int NKS = L::NKS, NQ = L::NQ, B = L::B;
   extern __shared__ float lds[];
   const int R = prm.R, M = prm.M, K = prm.K, HALF = prm.R / 2;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int64_t few = prm.P;                   // coop: as in encode16_kernel
-  bool coop = false;
-  if constexpr (MARKED) {
-    const int n = enc::block_marks<32>(prm, 4, lane, lds, few);
-    if (n == 0) return;
-    coop = prm.xch > 0 && n <= 32;
-  }
   float* sA = lds;                       // [NG][NKS][64]
   float* sHat = sA + NG * NKS * 64;      // [NG*16][B]
   float* sCs = sHat + NG * 16 * B;       // [2][NQ][R]
@@ -75,6 +66,7 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
   }
   __syncthreads();
 
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 31, u = lane >> 5;
   const LsTables tb{prm.gramH, prm.gramH64, prm.cs64, prm.xhat, M, R, kCondMaxFp32};
   unsigned n64 = 0;
@@ -82,9 +74,9 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
 #pragma unroll
   for (int q = 0; q < NQ; ++q) F[q] = prm.dftA[q * 64 + lane];
 
-  enc::WavePatches<32, MARKED> tiles(prm, 4, wave);
-  bool first = true;
-  for (int64_t p = few; MARKED && coop ? first : tiles.next(lane, p); first = false) {
+  const int64_t nwt = (prm.P + 31) / 32;
+  for (int64_t wt = int64_t(blockIdx.x) * 4 + wave; wt < nwt; wt += int64_t(gridDim.x) * 4) {
+    const int64_t p = wt * 32 + col;
     const bool valid = p < prm.P;
     float res[NKS];
     static_for<NKS>([&](auto J) {
@@ -105,8 +97,7 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
       // ---------------- (b) pass 1: best atom by its maximum over all angles
       float best = -1.f;
       int bm = 0;
-      const int g0 = MARKED && coop ? wave : 0, gs = MARKED && coop ? 4 : 1;
-      for (int g = g0; g < NG; g += gs) {
+      for (int g = 0; g < NG; ++g) {
         const float* Ag = sA + g * NKS * 64 + lane;
         f32x16 acc[NQ];
 #pragma unroll
@@ -177,7 +168,6 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
         }
         bm = upd ? g * 16 + ba : bm;
       }
-      if (MARKED && coop) enc::block_best<32>(lds + prm.xch, 4, wave, lane, best, bm);
       // ---------------- (b) pass 2: angles of the best atom, its stage-2 operand formed
       // again from its dictionary row (no per-atom copy is kept in pass 1)
       int rs;
@@ -222,8 +212,7 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
       n64 += (ls_update<L, KMAX>(st, ls, it, bm, rs, cval, sHat, sCs, tb, p, u, res) && u == 0) ? 1u : 0u;
     }
     const float rn2 = norm2<L>(res);
-    if (MARKED && coop && wave > 0) n64 = 0;
-    if (valid && u == 0 && !(MARKED && coop && wave > 0)) write_codes<L, KMAX>(prm, p, st, rn2);
+    if (valid && u == 0) write_codes<L, KMAX>(prm, p, st, rn2);
   }
   count_fp64(prm.stats, n64, lane);
 }
@@ -231,28 +220,18 @@ __global__ __launch_bounds__(256, 2) void encode32_kernel(EncodeParams prm, int 
 // ============================================================== launchers
 template <int S, int T, int KMAX>
 int launch32(const DeviceTables& t, const EncodeParams& prm, hipStream_t st) {
-  size_t lds = encode_lds_bytes(t, RSC_TILE_32);
-  const EncodeParams q = enc::with_exchange(prm, lds);
-  return launch_persistent(prm.marked ? encode32_kernel<S, T, KMAX, true> : encode32_kernel<S, T, KMAX, false>, lds,
-                           (prm.P + 31) / 32, t.enc_bpc, st, q, t.NG);
+  return launch_persistent(encode32_kernel<S, T, KMAX>, encode_lds_bytes(t, RSC_TILE_32), (prm.P + 31) / 32,
+                           t.enc_bpc, st, prm, t.NG);
 }
 
 template <class C, int HT, int KMAX, bool SPLIT>
 int launch16(const DeviceTables& t, const EncodeParams& prm, hipStream_t st) {
   const int64_t tiles = (prm.P + 15) / 16;
-  const bool irows = encode16_irows(t);
-  size_t lds = encode16_lds_bytes(t, irows);
-  const EncodeParams q = enc::with_exchange(prm, lds);
-  const int threads = irows ? encode16_threads(tiles) : 256;
-  auto run = [&](auto kern) { return launch_persistent_n(kern, threads, lds, tiles, t.enc_bpc, st, q); };
-  // the screened encoder has R <= 64: at most two angle tiles with the split, four without
-  if constexpr (HT <= (SPLIT ? 2 : 4))
-    if (prm.marked)
-      return irows ? run(encode16_kernel<C, HT, KMAX, SPLIT, true, true>)
-                   : run(encode16_kernel<C, HT, KMAX, SPLIT, false, true>);
-  if (prm.marked) return int(hipErrorInvalidValue);
-  return irows ? run(encode16_kernel<C, HT, KMAX, SPLIT, true, false>)
-               : run(encode16_kernel<C, HT, KMAX, SPLIT, false, false>);
+  if (encode16_irows(t))
+    return launch_persistent_n(encode16_kernel<C, HT, KMAX, SPLIT, true>, encode16_threads(tiles),
+                               encode16_lds_bytes(t, true), tiles, t.enc_bpc, st, prm);
+  return launch_persistent(encode16_kernel<C, HT, KMAX, SPLIT, false>, encode16_lds_bytes(t, false), tiles,
+                           t.enc_bpc, st, prm);
 }
 
 template <class C, int HT, bool SPLIT>
@@ -348,19 +327,19 @@ double encode_mfma_flops_per_patch(const DeviceTables& t, int tile, int K) {
 }
 
 int launch_encode(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
-                  int32_t* angle, float* coef, float* resid2, void* stream, bool marked) {
+                  int32_t* angle, float* coef, float* resid2, void* stream) {
   if (P <= 0) return 0;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (tile == RSC_TILE_32) {
     if (!tile32_usable(t, K)) return int(hipErrorInvalidValue);
     EncodeParams prm{xhat, P, K, t.M, t.R, t.dictA, t.dictHat, t.dftA32, t.cs, t.gramH, t.gramH64, t.cs64,
-                     atom, angle, coef, resid2, t.lpStats, nullptr, marked};
+                     atom, angle, coef, resid2, t.lpStats, nullptr};
     return r32(t, prm, st);
   }
   EncodeParams prm{xhat, P, K, t.M, t.R, nullptr, t.dictHat, t.R % 2 == 0 ? t.dftA16s : t.dftA16, t.cs, t.gramH,
-                   t.gramH64, t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI, marked};
+                   t.gramH64, t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI};
   if (t.geo == kGeoAnnular11 || t.geo == kGeoAnnular15)
-    return launch_encode_annular(t, xhat, P, K, atom, angle, coef, resid2, stream, marked);
+    return launch_encode_annular(t, xhat, P, K, atom, angle, coef, resid2, stream);
   if (t.geo != kGeoGrid) return int(hipErrorInvalidValue);
   if (t.S == 5 && t.T == 5) return r16<UniformCounts<5, 5>>(t, prm, st);
   if (t.S == 7 && t.T == 7) return r16<UniformCounts<7, 7>>(t, prm, st);

@@ -29,106 +29,7 @@ struct EncodeParams {
   float* resid2;
   unsigned long long* stats;   // [4]: [3] counts pursuit steps solved in FP64
   const float* dictHatI;       // i * dictionary rows, as dictHat (16x16 tile with IROWS; else unused)
-  bool marked;                 // code only the patches whose first atom is kTieMark (host: MARKED)
-  unsigned xch = 0;            // > 0: floats before the exchange area [waves][2][patches] in LDS
 };
-
-// The patches of a wave, TP at a time: its tiles wt, wt + stride, ... in turn, or (marked) the
-// marked patches of these tiles gathered, so that a wave with few of them runs one tile's pursuit
-// for all of them.  Where the whole block has no more than one tile of them (block_marks), its waves
-// share the atoms instead, 4 or 8 groups at a time (with few ties the launch is the latency of one
-// tile's pursuit: images of 2.3M windows, 128 atoms, 6 steps 0.40 -> 0.13 ms, 58,564 windows 0.24 ->
-// 0.12, 10^6 patches of 64 atoms, 4 steps 0.116 -> 0.087, 250k annular ones 0.138 -> 0.073).
-template <int TP, bool MARKED>
-struct WavePatches {
-  const EncodeParams& prm;
-  int64_t wt, stride, base = 0;
-  unsigned long long rest = 0;   // marked patches of the tiles from base on that were not yet given
-  __device__ __forceinline__ WavePatches(const EncodeParams& prm, int NW, int wave)
-      : prm(prm), wt(int64_t(blockIdx.x) * NW + wave), stride(int64_t(gridDim.x) * NW) {}
-  // Sets this lane's patch (P or beyond: none); false after the last.
-  __device__ __forceinline__ bool next(int lane, int64_t& p) {
-    const int64_t nwt = (prm.P + TP - 1) / TP;
-    if constexpr (!MARKED) {
-      p = wt * TP + lane % TP;
-      wt += stride;
-      return wt - stride < nwt;
-    }
-    p = prm.P;
-    int n = 0;
-    while (n < TP) {
-      if (rest == 0) {           // the marks of 64 / TP tiles at once
-        if (wt >= nwt) break;
-        base = wt;
-        const int64_t q = (wt + lane / TP * stride) * TP + lane % TP;
-        rest = __ballot(q < prm.P && prm.atom[q * prm.K] == kTieMark);
-        wt += 64 / TP * stride;
-        continue;
-      }
-      const int b = __builtin_ctzll(rest);
-      rest &= rest - 1;
-      if (lane % TP == n) p = (base + b / TP * stride) * TP + b % TP;
-      ++n;
-    }
-    return n > 0;
-  }
-};
-
-// The marked patches of this block's tiles (TP patches each, tile wt to wave wt % NW of its block):
-// their number, and this lane's one of the first TP (P: none), by way of the start of the dynamic
-// LDS.  Every thread reads patches of its own, so the scan has the block's loads in flight at
-// once; a block without a mark ends before it fills its tables.
-template <int TP>
-__device__ __forceinline__ int block_marks(const EncodeParams& prm, int NW, int lane, void* lds, int64_t& p) {
-  int64_t* list = reinterpret_cast<int64_t*>(lds);
-  int* count = reinterpret_cast<int*>(list + TP);
-  if (threadIdx.x == 0) *count = 0;
-  __syncthreads();
-  const int64_t per = int64_t(NW) * TP, step = per * gridDim.x;
-#pragma unroll 4
-  for (int64_t b = int64_t(blockIdx.x) * per + threadIdx.x % per + threadIdx.x / per * step; b < prm.P;
-       b += blockDim.x / per * step)
-    if (prm.atom[b * prm.K] == kTieMark) {
-      const int i = atomicAdd(count, 1);
-      if (i < TP) list[i] = b;
-    }
-  __syncthreads();
-  const int n = *count;
-  p = lane % TP < n ? list[lane % TP] : prm.P;
-  __syncthreads();                                  // the tables take the list's place
-  return n;
-}
-
-// The block's best atom of each patch, from its waves' (patch lane % TP, the same in the patch's
-// lanes): the larger maximum, the smaller atom on equal ones, as in one wave's scan of all atoms.
-template <int TP>
-__device__ __forceinline__ void block_best(float* xch, int NW, int wave, int lane, float& best, int& bm) {
-  float* xm = xch;
-  int* xa = reinterpret_cast<int*>(xch + NW * TP);
-  if (lane < TP) {
-    xm[wave * TP + lane] = best;
-    xa[wave * TP + lane] = bm;
-  }
-  __syncthreads();
-  for (int w = 0; w < NW; ++w) {
-    const float m = xm[w * TP + lane % TP];
-    const int a = xa[w * TP + lane % TP];
-    const bool take = m > best || (m == best && a < bm);
-    best = take ? m : best;
-    bm = take ? a : bm;
-  }
-  __syncthreads();
-}
-
-// A marked launch's exchange area past the tables, where it fits.
-constexpr size_t kExchangeBytes = 1024;
-inline EncodeParams with_exchange(EncodeParams prm, size_t& lds) {
-  if (prm.marked && lds + kExchangeBytes <= 160 * 1024) {
-    prm.xch = unsigned(lds / sizeof(float));
-    lds += kExchangeBytes;
-  }
-  return prm;
-}
 
 // Adds this wave's count of FP64 least-squares steps to stats[3] (one atomic per wave).
 __device__ __forceinline__ void count_fp64(unsigned long long* stats, unsigned n, int lane) {
@@ -212,9 +113,7 @@ __device__ __forceinline__ void atom_products4(const float* __restrict__ hat, in
 // the Re rows read d, so no lane applies a sign; without it (dictionaries too large for two
 // tables) the Im rows negate what they read.  Blocks of 4 or 8 waves (256 or 512 threads;
 // with 8, one block per CU shares the tables).
-// MARKED: only the patches that the screened encoder left to this form (a variant of its own: the
-// plain one lost 2 to 3% with both in one).
-template <class C, int HT, int KMAX, bool SPLIT, bool IROWS, bool MARKED>
+template <class C, int HT, int KMAX, bool SPLIT, bool IROWS>
 __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodeParams prm) {
   using L = LayoutBase<C, 4>;
   const int NW = int(blockDim.x) >> 6;                       // waves per block (4 or 8)
@@ -226,16 +125,6 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
   extern __shared__ float lds[];
   const int R = prm.R, M = prm.M, K = prm.K, HALF = SPLIT ? prm.R / 2 : prm.R;
   const int NG = (M + 7) / 8;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // coop: the block codes one tile of marked patches, each wave the correlations of its share of
-  // the atoms, and every wave the rest (the same values in all of them)
-  int64_t few = prm.P;
-  bool coop = false;
-  if constexpr (MARKED) {
-    const int n = block_marks<16>(prm, NW, lane, lds, few);
-    if (n == 0) return;
-    coop = prm.xch > 0 && n <= 16;
-  }
   float* sHat = lds;                              // [NG*8][B]
   float* sHatI = sHat + (IROWS ? NG * 8 * B : 0);  // [NG*8][B] with IROWS
   float* sCs = sHatI + NG * 8 * B;                // [2][NQ][R]
@@ -248,6 +137,7 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
   }
   __syncthreads();
 
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, u = lane >> 4;
   const LsTables tb{prm.gramH, prm.gramH64, prm.cs64, prm.xhat, M, R, kCondMaxFp32};
   unsigned n64 = 0;
@@ -272,9 +162,9 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
   auto k1_of = [](int q) { return SPLIT ? (q < SE ? 4 * q : 4 * (q - SE) + 1) : 2 * q; };
   auto k2_of = [](int q) { return SPLIT ? (q < SE ? 4 * q + 2 : 4 * (q - SE) + 3) : 2 * q + 1; };
 
-  WavePatches<16, MARKED> tiles(prm, NW, wave);
-  bool first = true;
-  for (int64_t p = few; MARKED && coop ? first : tiles.next(lane, p); first = false) {
+  const int64_t nwt = (prm.P + 15) / 16;
+  for (int64_t wt = int64_t(blockIdx.x) * NW + wave; wt < nwt; wt += int64_t(gridDim.x) * NW) {
+    const int64_t p = wt * 16 + col;
     const bool valid = p < prm.P;
     float res[NKS];
     static_for<NKS>([&](auto J) {
@@ -299,8 +189,7 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
       float bq = -1.f;
       int aq = 0;
       const int qperm = ((u & 1) << 1) | (u >> 1);   // atom of this quarter within a batch of 4
-      const int g0 = MARKED && coop ? wave : 0, gs = MARKED && coop ? NW : 1;
-      for (int g = g0; g < NG; g += gs) {
+      for (int g = 0; g < NG; ++g) {
         const float* hg = arow_hat + g * 8 * B;
         f32x4 acc[NQ];
 #pragma unroll
@@ -409,7 +298,6 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
         aq = take ? oa : aq;
       }
       bm = aq;
-      if (MARKED && coop) block_best<16>(lds + prm.xch, NW, wave, lane, bq, bm);
       // pass 2: the winner's stage-2 operand formed again from its dictionary row, then its
       // angles
       int rs;
@@ -470,8 +358,7 @@ __global__ __launch_bounds__(IROWS ? 512 : 256, 2) void encode16_kernel(EncodePa
       n64 += (ls_update<L, KMAX>(st, ls, it, bm, rs, cval, sHat, sCs, tb, p, u, res) && u == 0) ? 1u : 0u;
     }
     const float rn2 = norm2<L>(res);
-    if (MARKED && coop && wave > 0) n64 = 0;
-    if (valid && u == 0 && !(MARKED && coop && wave > 0)) write_codes<L, KMAX>(prm, p, st, rn2);
+    if (valid && u == 0) write_codes<L, KMAX>(prm, p, st, rn2);
   }
   count_fp64(prm.stats, n64, lane);
 }

@@ -10,8 +10,6 @@
 // steer each harmonic block by its own count.  Compiled for even R <= 64 and K <= 4.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "rsc_device.h"
 #include "rsc_encode16.h"
 #include "rsc_internal.h"
@@ -23,18 +21,11 @@ namespace {
 template <class C, int HT, int KMAX>
 int launchA(const DeviceTables& t, const enc::EncodeParams& prm, hipStream_t st) {
   const int64_t tiles = (prm.P + 15) / 16;
-  const bool irows = encode16_irows(t);
-  size_t lds = encode16_lds_bytes(t, irows);
-  const enc::EncodeParams q = enc::with_exchange(prm, lds);
-  const int threads = irows ? encode16_threads(tiles) : 256;
-  auto run = [&](auto kern) { return launch_persistent_n(kern, threads, lds, tiles, t.enc_bpc, st, q); };
-  if constexpr (std::is_same_v<C, AnnularCounts11>)
-    if (prm.marked)
-      return irows ? run(enc::encode16_kernel<C, HT, KMAX, true, true, true>)
-                   : run(enc::encode16_kernel<C, HT, KMAX, true, false, true>);
-  if (prm.marked) return int(hipErrorInvalidValue);
-  return irows ? run(enc::encode16_kernel<C, HT, KMAX, true, true, false>)
-               : run(enc::encode16_kernel<C, HT, KMAX, true, false, false>);
+  if (encode16_irows(t))
+    return launch_persistent_n(enc::encode16_kernel<C, HT, KMAX, true, true>, encode16_threads(tiles),
+                               encode16_lds_bytes(t, true), tiles, t.enc_bpc, st, prm);
+  return launch_persistent(enc::encode16_kernel<C, HT, KMAX, true, false>, encode16_lds_bytes(t, false), tiles,
+                           t.enc_bpc, st, prm);
 }
 
 template <class C>
@@ -47,11 +38,11 @@ int dispatchA(const DeviceTables& t, const enc::EncodeParams& prm, hipStream_t s
 }  // namespace
 
 int launch_encode_annular(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom,
-                          int32_t* angle, float* coef, float* resid2, void* stream, bool marked) {
+                          int32_t* angle, float* coef, float* resid2, void* stream) {
   if (P <= 0) return 0;
   if (K < 1 || K > kAnnularMaxK || t.R % 2 != 0 || t.R > kAnnularMaxR) return int(hipErrorInvalidValue);
   const enc::EncodeParams prm{xhat, P, K, t.M, t.R, nullptr, t.dictHat, t.dftA16s, t.cs, t.gramH, t.gramH64,
-                              t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI, marked};
+                              t.cs64, atom, angle, coef, resid2, t.lpStats, t.dictHatI};
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (t.geo == kGeoAnnular11) return dispatchA<AnnularCounts11>(t, prm, st);
   if (t.geo == kGeoAnnular15) return dispatchA<AnnularCounts15>(t, prm, st);

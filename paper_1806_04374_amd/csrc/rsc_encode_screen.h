@@ -29,10 +29,25 @@
 //     maxima are kept for this as FP16 fractions of ||r|| in private memory, which is read only
 //     for candidates, with a margin of 2^-10 for their rounding.  FP16's window holds about one
 //     atom, and the bookkeeping would cost more than it saves.
-//   ties (FP32 handles, ScreenParams::tie): where another atom or angle comes within the rounding
-//     of the FP32 sums, the patch is marked and the full FP32 encoder codes it in a second launch
-//     (the rule and its figures: screen_resolves, rsc_encode_screen.hip).
 //   least squares and residual update in FP32 (ls_step), as in the FP32 encoders.
+//
+// FP32 handles (FULL) get the codes of the full form that they would run without a screen, bit for
+// bit, so that no patch depends on which form coded it.  v_mfma_f32_32x32x2f32 and _16x16x4f32 add
+// their terms one after the other, each rounded as an fmaf (checked over 384,000 results with
+// exponents up to 2^100 apart), so the full form's sums can be formed here:
+//   second pass: C_k and the residual norms summed as the full form's lanes hold the coordinates
+//     (W = 2: the 32x32 tile; W = 4, the 16x16 tile: even and odd profiles apart), the angle DFT with its
+//     parity split.  All candidates are scored like this, so the winner's angle and correlation are
+//     the full form's, and with ls_step's sums so are the coefficients and the residual.
+//   first pass, which chooses the atom: C_k as one chain over (Re, Im) of one profile after the
+//     other, the order of the stage-1 instructions in both tiles.  Where the two largest maxima are
+//     further apart than the rounding of both passes (tie_window) both choose the same atom; otherwise
+//     the patch's candidates are scored once more in this order.  Of random patches about one step
+//     in a thousand needs that; where atoms coincide every step does, and pays for one more scoring of
+//     its candidates: with every atom twice in the dictionary 10^6 11x11 patches (M = 64, K = 4) take 1.50
+//     ms against 1.07 with distinct atoms and 3.39 in the full form.  A dictionary whose atoms all
+//     agree to 1e-6 leaves the screen nothing to leave out (9.5 ms).  (Rounds of one loop in place of
+//     a second copy of the scoring code are 1 to 6% slower.)
 //
 // What bounds it: vector issue.  A wave's maxima over 64 angles cost 16 three-way maxima per
 // atom for 32 patches, and the 16-bit products take as many cycles on the matrix cores, so
@@ -41,6 +56,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "rsc_device.h"
 #include "rsc_internal.h"
@@ -72,7 +89,6 @@ struct ScreenParams {
   unsigned long long* stats;   // [4], see rsc_precision_stats
   float cond_max;              // least squares in FP64 beyond this bound (ls_update)
   bool count;                  // whether candidates are counted (16-bit handles)
-  float tie;                   // > 0: patches with a selection decided by less than tie ||r|| get kTieMark
   int32_t* label;              // not null: no codes; each patch keeps the smaller of sse and its squared
   float* sse;                  // residual norm, and class cls with it where that is the smaller (class 0
   int cls;                     // always), as classify_min_kernel
@@ -207,35 +223,67 @@ struct RowBatches {
 };
 
 // C_k = sum_s conj(d_{m,s,k}) x_{s,k} of the atom in `row` for this lane's patch: op[k] = Re C_k in
-// the low half-wave and Im C_k in the high one (atom_operand, on a row of pairs).  Each half-wave
-// multiplies its residual coordinates (Re parts low, Im parts high) with both parts of the
-// atom, and one swap per harmonic adds the halves' sums.
-template <class L>
+// the low half-wave and Im C_k in the high one, on a row of pairs.  Each half-wave multiplies its
+// residual coordinates (Re parts low, Im parts high) with both parts of the atom, and one swap per
+// harmonic adds the halves' sums: the order of atom_operand.  W = 4: even and odd profiles are
+// summed apart, the order of atom_products4.
+template <class L, int W>
 __device__ __forceinline__ void row_operand(const float* __restrict__ row, int u, const float (&res)[L::NKS],
                                             float (&op)[L::NQ]) {
   float d0[L::J0];
 #pragma unroll
   for (int j = 0; j < L::J0; ++j) d0[j] = row[2 * j + u];
-  float pr[L::NQ], pi[L::NQ];
-  zero(pr);
-  zero(pi);
+  constexpr int NC = W / 2;                          // chains per sum
+  float pr[NC][L::NQ], pi[NC][L::NQ];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    zero(pr[c]);
+    zero(pi[c]);
+  }
   RowBatches<L>::template each<false>(row, u, [&](auto K1, auto I, float re, float im) {
-    constexpr int k = decltype(K1)::value, j = L::joff(k) + decltype(I)::value;
-    pr[k] = fmaf(re, res[j], pr[k]);
-    pi[k] = fmaf(im, res[j], pi[k]);
+    constexpr int k = decltype(K1)::value, j = L::joff(k) + decltype(I)::value, c = decltype(I)::value % NC;
+    pr[c][k] = fmaf(re, res[j], pr[c][k]);
+    pi[c][k] = fmaf(im, res[j], pi[c][k]);
   }, [&](auto K1) {
     // low (Re x): Re += dRe x, Im -= dIm x; high (Im x): Re += dIm x, Im += dRe x
     constexpr int k = decltype(K1)::value;
-    float x = u ? pi[k] : pr[k], y = u ? pr[k] : -pi[k];
-    swap32(x, y);
-    op[k] = x + y;
-  });
-  float p0 = 0.f;
 #pragma unroll
-  for (int j = 0; j < L::J0; ++j) p0 = fmaf(d0[j], res[j], p0);
-  float x = p0, y = 0.f;
-  swap32(x, y);
-  op[0] = x + y;
+    for (int c = 0; c < NC && c < L::Sk(k); ++c) {
+      float x = u ? pi[c][k] : pr[c][k], y = u ? pr[c][k] : -pi[c][k];
+      swap32(x, y);
+      op[k] = c == 0 ? x + y : op[k] + (x + y);
+    }
+  });
+#pragma unroll
+  for (int c = 0; c < NC && c < L::J0; ++c) {
+    float x = 0.f, y = 0.f;
+#pragma unroll
+    for (int j = c; j < L::J0; j += NC) x = fmaf(d0[j], res[j], x);
+    swap32(x, y);
+    op[0] = c == 0 ? x + y : op[0] + (x + y);
+  }
+}
+
+// The same C_k in the order of the full form's first pass: one chain over the profiles, each
+// profile's product with Re x before the one with Im x (harmonic 0: one chain over the profiles).
+template <class L>
+__device__ __forceinline__ void chain_operand(const float* __restrict__ row, int u, const float (&res)[L::NKS],
+                                              float (&op)[L::NQ]) {
+  zero(op);
+#pragma unroll
+  for (int j = 0; j < L::J0; ++j) {
+    float x = res[j], y = res[j];
+    swap32(x, y);                                    // profiles 2j and 2j + 1, in both half-waves
+    op[0] = fmaf(row[2 * j + 1], y, fmaf(row[2 * j], x, op[0]));
+  }
+  op[0] = u ? 0.f : op[0];
+  RowBatches<L>::template each<true>(row, u, [&](auto K1, auto I, float own, float oth) {
+    constexpr int k = decltype(K1)::value, j = L::joff(k) + decltype(I)::value;
+    float x = res[j], y = res[j];
+    swap32(x, y);                                    // Re x and Im x
+    // Re C: dRe Re x, then dIm Im x; Im C: -dIm Re x, then dRe Im x
+    op[k] = fmaf(oth, y, fmaf(u ? -own : own, x, op[k]));
+  }, [](auto) {});
 }
 
 // acc += alpha S_r d for the atom in `row` on this lane's coordinates; cs: (cos, sin) of this
@@ -269,7 +317,7 @@ __device__ __forceinline__ void row_axpy(float (&acc)[L::NKS], float alpha, cons
 // The least-squares step of ls_update (same formulas and thresholds) with what it indexes by
 // slot at run time kept in the wave's LDS, `mem`: one copy of the code steers every selected
 // column, instead of one per slot, and the half-waves share the pair products (slot 2i + u).
-template <class L, int KMAX>
+template <class L, int KMAX, int W>
 __device__ __forceinline__ bool ls_step(PursuitState<KMAX>& st, LsState<KMAX>& ls, int it, int ms, int rs, float cval,
                                         const float* pairs, int row, const float2* cs, const LsTables& tb,
                                         const float* norm2, const float* hat, int64_t p, int u, int col, float* mem,
@@ -378,7 +426,7 @@ __device__ __forceinline__ bool ls_step(PursuitState<KMAX>& st, LsState<KMAX>& l
   for (int i = 0; i < KMAX; ++i) st.cf[i] = (up32 && i <= it) ? an[i] : st.cf[i];
   ls.condF = up32 ? Fn : ls.condF;
   bool ok64 = false;
-  if (__any(go64)) ok64 = ls_solve64<L, KMAX>(st, it, ms, rs, go64, hat, tb, p, u, res);
+  if (__any(go64)) ok64 = ls_solve64<L, KMAX, W>(st, it, ms, rs, go64, hat, tb, p, u, res);
   ls.fp64 = ls.fp64 || ok64;
   st.nsel = (up32 || ok64) ? it + 1 : st.nsel;
   st.active = up32 || ok64;
@@ -410,10 +458,21 @@ __host__ __device__ constexpr size_t screen_table_bytes(int NG, int NJ, int NQ, 
   return size_t(NG) * NJ * 1024 + ((sizeof(float) * (size_t(rows) * row + 2 * size_t(NQ | 1) * R + size_t(FT) * NQ * 64) + 15) & ~size_t(15));
 }
 
+// How far, in units of ||r||, the largest maximum of one pass can lie below the other pass's and still
+// win there: twice what the passes can differ by in one score.  With u = 2^-24 and a_k = sum_s |d_s|
+// |r_s| over harmonic k, the parts of C_k are rounded at most 2S times in the first pass and S + 2 times
+// in the second, each by u a_k, and the angle DFT rounds each |C_k| <= a_k at most T + 3 times with
+// the parity split and 2T + 2 without, in either pass.  The a_k add up to at most ||d|| ||r||, and
+// |cos| + |sin| to sqrt(2).  (4u more for the norm and higher orders: 84u at 11x11, 109u at 15x15.)
+constexpr float tie_window(int S, int T, bool split) {
+  return (2 * (1.4143f * (3 * S + 2) + 2 * (split ? T + 3 : 2 * T + 2)) + 4) * 0x1p-24f;
+}
+
 // RT: 32-angle tiles of the screen (ceil(R / 32)).  SPLIT: the FP32 scores use the radix-2
 // angle split (even R, R/2 <= 32 rows: E from even harmonics, O from odd ones, score(r) = E + O
-// and score(r + R/2) = E - O); otherwise RT tiles of the direct angle DFT.
-template <class C, int KMAX, int PREC, int RT, bool SPLIT>
+// and score(r + R/2) = E - O); otherwise RT tiles of the direct angle DFT.  W, FULL: the order of
+// the FP32 sums (above).
+template <class C, int KMAX, int PREC, int RT, bool SPLIT, int W, bool FULL>
 __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm) {
   using L = LayoutBase<C, 2>;
   using P = Lp<PREC>;
@@ -458,6 +517,8 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
   constexpr bool kFilter = PREC == RSC_BF16;
   constexpr float efac = 4.25f * P::unit + 0x1p-10f;
   static_assert(!kFilter || HA == 8, "the filter keeps 8 maxima per lane and group");
+  constexpr float ktie = tie_window(L::S, T, SPLIT);
+  static_assert(!kFilter || !FULL, "the full form's atoms are compared in increasing order");
   uint4 vmax[kFilter ? 8 : 1];   // [groups] 8 FP16 fractions: this lane's maxima of the step
   unsigned n_sel = 0, n_cand = 0, n_fp64 = 0, max_cand = 0;
 
@@ -469,15 +530,14 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
     const bool valid = p < prm.P;
     float res[NKS];
     load_hat<L>(prm.xhat + (valid ? p : prm.P - 1) * B, u, valid, res);
-    const float nx2 = norm2<L>(res);
+    const float nx2 = norm2<L, W>(res);
     PursuitState<KMAX> st;
     init_state(st, valid);
     LsState<KMAX> ls;
     init_ls(ls);
-    bool tied = false;
 
     for (int it = 0; it < K; ++it) {
-      const float n2 = norm2<L>(res);
+      const float n2 = norm2<L, W>(res);
       st.active = st.active && (n2 > kTau2 * nx2);
       if (!__any(st.active)) break;
       StateIo<KMAX>::save(sState, lane, st, ls);
@@ -615,24 +675,8 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
 #pragma unroll
         for (int t = 0; t < FT; ++t) E[t][i] = 0.f;
       }
-      for (int pass = 0;; ++pass) {
-        int m;
-        bool has;
-        if (kFilter && pass == 0) {
-          m = m1;
-          has = has1;
-        } else {
-          const int mine = mask ? 2 * int(__builtin_ctzll(mask)) + u : 0x7fffffff;
-          m = min(mine, other_half(mine, u));
-          has = m != 0x7fffffff;
-          if (has && mine == m) mask &= mask - 1;
-        }
-        if (!__any(has)) break;
-        nc += has ? 1 : 0;
-        const int mc = has ? m : 0;
-        float op32[NQ];
-        row_operand<L>(sHat + mc * RB, u, res, op32);
-        f32x16 e[FT], o;
+      // the atom's scores over all angles from its C_k, and the largest of them
+      auto scores = [&](const float (&op32)[NQ], f32x16 (&e)[FT], f32x16& o) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i] = 0.f;
 #pragma unroll
@@ -650,10 +694,30 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         for (int t = 0; t < FT; ++t)
 #pragma unroll
           for (int i = 0; i < 16; ++i) cm = fmaxf(cm, SPLIT ? fabsf(e[t][i]) + fabsf(o[i]) : fabsf(e[t][i]));
-        cm = max_halves_nonneg(cm);
+        return max_halves_nonneg(cm);
+      };
+      // takes the patch's smallest candidate out of its lanes' masks; false if there is none
+      auto next = [&](uint64_t& left, int& m) {
+        const int mine = left ? 2 * int(__builtin_ctzll(left)) + u : 0x7fffffff;
+        m = min(mine, other_half(mine, u));
+        const bool has = m != 0x7fffffff;
+        if (has && mine == m) left &= left - 1;
+        return has;
+      };
+      const uint64_t cand = mask;
+      for (int pass = 0;; ++pass) {
+        int m = m1;
+        const bool has = kFilter && pass == 0 ? has1 : next(mask, m);
+        if (!__any(has)) break;
+        nc += has ? 1 : 0;
+        const int mc = has ? m : 0;
+        float op32[NQ];
+        row_operand<L, W>(sHat + mc * RB, u, res, op32);
+        f32x16 e[FT], o;
+        const float cm = scores(op32, e, o);
         // equal maxima go to the smaller atom (without the filter the atoms come in order)
         const bool gt = has && (cm > best || (kFilter && cm == best && mc < bm));
-        if (!kFilter) second = has ? __builtin_amdgcn_fmed3f(best, cm, second) : second;   // second <= best
+        if (FULL) second = has ? __builtin_amdgcn_fmed3f(best, cm, second) : second;   // second <= best
         best = gt ? cm : best;
         bm = gt ? mc : bm;
 #pragma unroll
@@ -676,13 +740,46 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
           mask = keep;
         }
       }
+      // ---------------- where atoms tie, the one that the full form's first pass chooses (below a
+      // squared norm of 1e-30, where products underflow, every second candidate counts as a tie)
+      if constexpr (FULL) {
+        const bool tie = st.active && second >= (n2 > 1e-30f ? fmaxf(best - ktie * rn, 0.f) : 0.f);
+        if (__any(tie)) {
+          uint64_t left = tie ? cand : 0;
+          float b1 = -1.f, op32[NQ];
+          int a1 = bm, m;
+          f32x16 e[FT], o;
+          for (;;) {
+            const bool has = next(left, m);
+            if (!__any(has)) break;
+            const int mc = has ? m : 0;
+            chain_operand<L>(sHat + mc * RB, u, res, op32);
+            const float cm = scores(op32, e, o);
+            const bool gt = has && cm > b1;
+            b1 = gt ? cm : b1;
+            a1 = gt ? mc : a1;
+          }
+          const bool swap = a1 != bm;
+          if (__any(swap)) {
+            row_operand<L, W>(sHat + a1 * RB, u, res, op32);
+            const float cm = scores(op32, e, o);
+            best = swap ? cm : best;
+            bm = a1;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+#pragma unroll
+              for (int t = 0; t < FT; ++t) E[t][i] = swap ? e[t][i] : E[t][i];
+              if (SPLIT) O[i] = swap ? o[i] : O[i];
+            }
+          }
+        }
+      }
       // ---------------- angle of the best atom: the smallest angle index whose |score| is its
       // maximum.  max(|E| + |O|) is bit for bit the largest rounded |E + O| or |E - O|, so the
       // scores are compared with it for equality; rows past the valid angles score 0 and come
       // last.  The rows ascend with the register in each half-wave: searched from the last.
-      int rs = 0x7fffffff, near = 0;       // near: angles whose |score| is at least thr
+      int rs = 0x7fffffff;
       float cval = 0.f;
-      const float thr = best - prm.tie * rn;
       if (SPLIT) {
         const int HALF = R / 2;
 #pragma unroll
@@ -692,7 +789,6 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
             const float s = h == 0 ? E[0][i] + O[i] : E[0][i] - O[i];
             const bool eq = fabsf(s) == best;
             rs = eq ? 8 * (i / 4) + (i % 4) + 4 * u + h * HALF : rs;
-            if (!kFilter) near += fabsf(s) >= thr ? 1 : 0;
             cval = eq ? s : cval;
           }
       } else {
@@ -703,7 +799,6 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
             const float s = E[t][i];
             const bool eq = fabsf(s) == best;
             rs = eq ? 32 * t + 8 * (i / 4) + (i % 4) + 4 * u : rs;
-            if (!kFilter) near += fabsf(s) >= thr ? 1 : 0;
             cval = eq ? s : cval;
           }
       }
@@ -714,30 +809,6 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
         rs = oc < rs ? oc : rs;
         rs = rs < R ? rs : R - 1;
       }
-      // ---------------- whether another atom, or another angle of the best one, comes within the
-      // rounding of these sums.  Angles that tie at the spacing R / near are the symmetry of the
-      // atom (or of the patch) itself: any of them gives the same code, and the first one is kept
-      if (!kFilter && prm.tie > 0.f) {
-        near += other_half(near, u);
-        tied = tied || (st.active && second >= thr);
-        if (__any(st.active && near > 1)) {
-          int lo = 0x7fffffff, hi = -1;
-          float thr2 = thr;
-          asm volatile("" : "+v"(thr2));   // compared again: 32 masks kept from above would spill
-#pragma unroll
-          for (int t = 0; t < (SPLIT ? 2 : FT); ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const float s = SPLIT ? (t == 0 ? E[0][i] + O[i] : E[0][i] - O[i]) : E[t % FT][i];
-              const int r = 8 * (i / 4) + (i % 4) + 4 * u + t * (SPLIT ? R / 2 : 32);
-              lo = fabsf(s) >= thr2 ? min(lo, r) : lo;
-              hi = fabsf(s) >= thr2 ? max(hi, r) : hi;
-            }
-          lo = min(lo, other_half(lo, u));
-          hi = max(hi, other_half(hi, u));
-          tied = tied || (st.active && near > 1 && hi - lo != R - R / near);
-        }
-      }
       // ---------------- least squares
       wave_lds_order();
       StateIo<KMAX>::load(sState, col, st, ls);
@@ -745,10 +816,10 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       n_sel += nc > 0 ? 1 : 0;
       n_cand += nc;
       max_cand = nc > max_cand ? nc : max_cand;
-      n_fp64 += ls_step<L, KMAX>(st, ls, it, bm, rs, cval, sHat, RB, sCs, tb, prm.norm2, prm.dictHat, p, u, col,
+      n_fp64 += ls_step<L, KMAX, W>(st, ls, it, bm, rs, cval, sHat, RB, sCs, tb, prm.norm2, prm.dictHat, p, u, col,
                                  reinterpret_cast<float*>(sState), res) ? 1 : 0;
     }
-    const float rn2 = norm2<L>(res);
+    const float rn2 = norm2<L, W>(res);
     if (prm.label) {
       if (valid && u == 0 && (prm.cls == 0 || rn2 < prm.sse[p])) {
         prm.sse[p] = rn2;
@@ -759,7 +830,7 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       for (int i = 0; i < KMAX; ++i) {
         if (i < K) {
           const bool s = i < st.nsel;
-          prm.atom[p * K + i] = i == 0 && tied ? kTieMark : s ? st.selm[i] : -1;
+          prm.atom[p * K + i] = s ? st.selm[i] : -1;
           prm.angle[p * K + i] = s ? st.selr[i] : -1;
           prm.coef[p * K + i] = s ? st.cf[i] : 0.f;
         }
@@ -800,12 +871,12 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
 }
 
 // One launch: 8 waves per block where the tables and their states fit a CU's LDS, else 4.
-template <class C, int KMAX, int PREC, int RT, bool SPLIT>
+template <class C, int KMAX, int PREC, int RT, bool SPLIT, int W, bool FULL>
 int launch(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
   const int nw = screen_waves(t, KMAX);
   if (nw == 0) return int(hipErrorInvalidValue);
   const size_t lds = screen_lds_bytes(t, KMAX, nw);
-  auto kern = encode_screen_kernel<C, KMAX, PREC, RT, SPLIT>;
+  auto kern = encode_screen_kernel<C, KMAX, PREC, RT, SPLIT, W, FULL>;
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
@@ -819,11 +890,27 @@ int launch(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
   return int(hipGetLastError());
 }
 
+// 16-bit handles: the split for even R > 32, the order of sums of the 32x32 tile.
 template <class C, int KMAX, int PREC>
-int launch_angles(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
-  if (t.R <= 32) return launch<C, KMAX, PREC, 1, false>(t, prm, st);
-  if (t.lpSplit) return launch<C, KMAX, PREC, 2, true>(t, prm, st);
-  return launch<C, KMAX, PREC, 2, false>(t, prm, st);
+int launch_lp(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
+  if (t.R <= 32) return launch<C, KMAX, PREC, 1, false, 2, false>(t, prm, st);
+  if (t.lpSplit) return launch<C, KMAX, PREC, 2, true, 2, false>(t, prm, st);
+  return launch<C, KMAX, PREC, 2, false, 2, false>(t, prm, st);
+}
+
+// FP32 handles in the order of the 16x16 tile: the split for every even R.
+template <class C, int KMAX>
+int launch_full16(const DeviceTables& t, const ScreenParams& prm, hipStream_t st) {
+  if (t.lpSplit) {
+    if (t.R <= 32) return launch<C, KMAX, RSC_FP16, 1, true, 4, true>(t, prm, st);
+    return launch<C, KMAX, RSC_FP16, 2, true, 4, true>(t, prm, st);
+  }
+  if constexpr (std::is_same_v<C, AnnularCounts11>) {
+    return int(hipErrorInvalidValue);                // even R only
+  } else {
+    if (t.R <= 32) return launch<C, KMAX, RSC_FP16, 1, false, 4, true>(t, prm, st);
+    return launch<C, KMAX, RSC_FP16, 2, false, 4, true>(t, prm, st);
+  }
 }
 
 }  // namespace screen

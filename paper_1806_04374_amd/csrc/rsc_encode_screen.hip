@@ -4,7 +4,7 @@
 
 namespace rsc {
 
-int screen_grid11_fp16(const DeviceTables& t, const screen::ScreenParams& prm, void* stream);
+int screen_grid11_fp16(const DeviceTables& t, int tile, const screen::ScreenParams& prm, void* stream);
 int screen_grid15_fp16(const DeviceTables& t, const screen::ScreenParams& prm, void* stream);
 int screen_grid_bf16(const DeviceTables& t, const screen::ScreenParams& prm, void* stream);
 
@@ -21,20 +21,6 @@ size_t table_bytes(const DeviceTables& t) {
   const int ft = t.R <= 32 || t.lpSplit ? 1 : 2;
   return screen::screen_table_bytes(ng, screen_steps(t.T), t.T + 1, ng * ag, screen_row(t.B, t.sk[0]), t.R, ft);
 }
-
-// Ties.  Two scores closer than the rounding of their FP32 sums are ordered by that rounding, and a
-// patch's code differs from there on by which form summed them: 8 to 16 of 2.3M image windows
-// (128 atoms, 6 steps), 0 to 4 of 10^6 patches (64 atoms, 4 steps), where also the two full tile
-// shapes disagree, and some coefficients then differ by their whole size.  FP32 handles
-// therefore leave such patches to the full encoder, which codes them from the start: a step
-// is marked when another atom or angle comes within 2^-22 ||r|| of the selected one.  Of 28M image
-// windows none differed any more, where without it about 130 do; the gaps that flip are of the
-// size of the summation error, about 0.3 of that.
-// The second launch costs about 3 us where nothing is marked and the latency of one tile's pursuit
-// (50 to 130 us) where something is, so it is left out where the ties are rarest and the calls
-// shortest: for M K below 64 (2,000 patches, 16 atoms, 2 steps: 22 us with one launch, 25 with two).
-constexpr float kTieWindow = 0x1p-22f;
-constexpr int kTieWork = 64;
 
 }  // namespace
 
@@ -58,8 +44,6 @@ bool screen_usable(const DeviceTables& t, int K) {
   return t.scrPrec != RSC_FP32 && screen_waves(t, kmax_of(t, K)) > 0;
 }
 
-bool screen_resolves(const DeviceTables& t, int K) { return t.prec == RSC_FP32 && t.M * K >= kTieWork; }
-
 double screen_mfma_flops_per_patch(const DeviceTables& t, int K) {
   // per step and 32 patches: the stage-1 and stage-2 32x32x16 instructions of every group
   const int ag = screen_group_atoms(t.T), ops = screen_ops(t.T), ng = (t.M + ag - 1) / ag, rt = t.R <= 32 ? 1 : 2;
@@ -67,23 +51,23 @@ double screen_mfma_flops_per_patch(const DeviceTables& t, int K) {
   return double(K) * ng * (screen_steps(t.T) + double(ag) * rt * ops) * per_instr / 32.0;
 }
 
-int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                         float* coef, float* resid2, void* stream, bool mark, ClassOut cls) {
+int launch_encode_screen(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
+                         int32_t* angle, float* coef, float* resid2, void* stream, ClassOut cls) {
   if (P <= 0) return 0;
   const screen::ScreenParams prm{xhat, P, K, t.M, t.R,
                                  reinterpret_cast<const uint4*>(t.lpA), t.dictPairs, t.dictHat,
                                  reinterpret_cast<const uint4*>(t.lpF16), t.lpF32, t.cs, t.gramH, t.norm2, t.gramH64, t.cs64,
                                  atom, angle, coef, resid2, t.lpStats,
                                  t.prec == RSC_FP32 ? kCondMaxFp32 : kCondMax16, t.prec != RSC_FP32,
-                                 mark ? kTieWindow : 0.f, cls.label, cls.sse, cls.c};
+                                 cls.label, cls.sse, cls.c};
   if (t.geo == kGeoAnnular11) {
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (K <= 2) return screen::launch_angles<AnnularCounts11, 2, RSC_FP16>(t, prm, st);
-    return screen::launch_angles<AnnularCounts11, 4, RSC_FP16>(t, prm, st);
+    if (K <= 2) return screen::launch_full16<AnnularCounts11, 2>(t, prm, st);
+    return screen::launch_full16<AnnularCounts11, 4>(t, prm, st);
   }
   if (t.scrPrec == RSC_BF16) return screen_grid_bf16(t, prm, stream);
   if (t.scrPrec != RSC_FP16) return int(hipErrorInvalidValue);
-  return t.T == 5 ? screen_grid11_fp16(t, prm, stream) : screen_grid15_fp16(t, prm, stream);
+  return t.T == 5 ? screen_grid11_fp16(t, tile, prm, stream) : screen_grid15_fp16(t, prm, stream);
 }
 
 }  // namespace rsc

@@ -3,13 +3,23 @@
 
 namespace rsc {
 
-int screen_grid11_fp16(const DeviceTables& t, const screen::ScreenParams& prm, void* stream) {
+int screen_grid11_fp16(const DeviceTables& t, int tile, const screen::ScreenParams& prm, void* stream) {
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   using C = UniformCounts<5, 5>;
-  if (prm.K <= 2) return screen::launch_angles<C, 2, RSC_FP16>(t, prm, st);
-  if (prm.K <= 4) return screen::launch_angles<C, 4, RSC_FP16>(t, prm, st);
-  if (prm.K <= 6) return screen::launch_angles<C, 6, RSC_FP16>(t, prm, st);
-  return screen::launch_angles<C, 8, RSC_FP16>(t, prm, st);
+  if (t.prec == RSC_FP16) {
+    if (prm.K <= 2) return screen::launch_lp<C, 2, RSC_FP16>(t, prm, st);
+    if (prm.K <= 4) return screen::launch_lp<C, 4, RSC_FP16>(t, prm, st);
+    if (prm.K <= 6) return screen::launch_lp<C, 6, RSC_FP16>(t, prm, st);
+    return screen::launch_lp<C, 8, RSC_FP16>(t, prm, st);
+  }
+  if (tile == RSC_TILE_32) {   // even R in 34..64, K <= 4
+    if (prm.K <= 2) return screen::launch<C, 2, RSC_FP16, 2, true, 2, true>(t, prm, st);
+    return screen::launch<C, 4, RSC_FP16, 2, true, 2, true>(t, prm, st);
+  }
+  if (prm.K <= 2) return screen::launch_full16<C, 2>(t, prm, st);
+  if (prm.K <= 4) return screen::launch_full16<C, 4>(t, prm, st);
+  if (prm.K <= 6) return screen::launch_full16<C, 6>(t, prm, st);
+  return screen::launch_full16<C, 8>(t, prm, st);
 }
 
 }  // namespace rsc

@@ -75,7 +75,7 @@ struct DeviceTables {
   uint16_t* lpF16 = nullptr; // stage-2 operand [operands][ceil(R/32)][64][8]
   float* lpF32 = nullptr;    // FP32 re-score angle DFT operand: [T+1][64] rows r < R/2 when
                              // lpSplit, else [ceil(R/32)][T+1][64]
-  bool lpSplit = false;      // even R in 33..64: radix-2 split in the FP32 re-score
+  bool lpSplit = false;      // radix-2 split in the FP32 scores: even R (16-bit handles: even R > 32)
   double* gramH64 = nullptr; // FP64 pair table [M][M][2T+1]
   double* cs64 = nullptr;    // FP64 [2][T+1][R] cos, sin (every handle)
   unsigned long long* lpStats = nullptr;  // [4] counters (rsc_precision_stats)
@@ -103,10 +103,8 @@ int launch_dict_tables(const DictBuild& p, void* stream);
 
 // Kernel launchers.  Return a hipError_t as int.
 int launch_project(const DeviceTables& t, const float* patches, int64_t P, float* xhat, void* stream);
-// marked: only the patches whose first atom the screened encoder left at kTieMark.
-constexpr int kTieMark = -2;
 int launch_encode(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
-                  int32_t* angle, float* coef, float* resid2, void* stream, bool marked = false);
+                  int32_t* angle, float* coef, float* resid2, void* stream);
 int launch_synthesize(const DeviceTables& t, const int32_t* atom, const int32_t* angle_idx,
                       const float* theta, const float* weight, int64_t P, int J,
                       const float* noise, float* out, void* stream);
@@ -118,7 +116,7 @@ bool encode_supported_geo(const DeviceTables& t);   // the encoder is compiled f
 // R <= 64, K <= 4.
 constexpr int kAnnularMaxK = 4, kAnnularMaxR = 64;
 int launch_encode_annular(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom,
-                          int32_t* angle, float* coef, float* resid2, void* stream, bool marked);
+                          int32_t* angle, float* coef, float* resid2, void* stream);
 size_t encode_lds_bytes(const DeviceTables& t, int tile);
 // 16x16 FP32 tile: LDS of one block with (irows) or without the i * dictionary copy, whether
 // the copy is used (both tables fit a CU), and the block size of a launch over wave_tiles
@@ -169,18 +167,16 @@ bool screen_usable(const DeviceTables& t, int K);
 size_t screen_lds_bytes(const DeviceTables& t, int kmax, int waves);
 int screen_waves(const DeviceTables& t, int kmax);
 double screen_mfma_flops_per_patch(const DeviceTables& t, int K);
-// mark: patches with a near tie are left with kTieMark for a marked launch_encode.  With cls.label the
-// codes (which may then be null) are not written: the patches' labels and errors take class cls.c in,
-// as by launch_classify_min after it.
+// tile: the full form (RSC_TILE_16 or RSC_TILE_32) whose codes an FP32 handle's are, bit for bit.  With
+// cls.label the codes (which may then be null) are not written: the patches' labels and errors take class
+// cls.c in, as by launch_classify_min after it.
 struct ClassOut {
   int32_t* label = nullptr;
   float* sse = nullptr;
   int c = 0;
 };
-int launch_encode_screen(const DeviceTables& t, const float* xhat, int64_t P, int K, int32_t* atom, int32_t* angle,
-                         float* coef, float* resid2, void* stream, bool mark, ClassOut cls = {});
-// Whether ties of the screened FP32 pursuit are resolved by the full FP32 form (rsc_encode_screen.hip).
-bool screen_resolves(const DeviceTables& t, int K);
+int launch_encode_screen(const DeviceTables& t, int tile, const float* xhat, int64_t P, int K, int32_t* atom,
+                         int32_t* angle, float* coef, float* resid2, void* stream, ClassOut cls = {});
 size_t images_workspace_bytes(int n_images);
 // rsc_project_images_noalloc: the plan in a static device array of this many images.
 constexpr int kNoAllocMaxImages = 65535;

@@ -127,10 +127,11 @@ def test_scaled_coordinates(dev, kind, N, power):
     h.close()
 
 
-@pytest.mark.parametrize("kind,N,M,R,K", [("grid", 11, 64, 64, 4), ("grid", 15, 100, 64, 6), ("annular", 11, 64, 64, 4)])
-def test_screen_agrees_with_fp32_tile(dev, kind, N, M, R, K):
+@pytest.mark.parametrize("kind,N,M,R,K,tile", [("grid", 11, 64, 64, 4, "32"), ("grid", 15, 100, 64, 6, "16"),
+                                               ("annular", 11, 64, 64, 4, "16")])
+def test_screen_agrees_with_fp32_tile(dev, kind, N, M, R, K, tile):
     """The same coordinates through the screen and through the FP32 tile that scores every atom:
-    the codes differ only where two FP32 scores tie to rounding."""
+    the same codes."""
     from paper_1806_04374_amd import rsc
     basis, h = _make(kind, N)
     D = wl.draw_dictionary(M, basis.B, seed=8)
@@ -138,12 +139,10 @@ def test_screen_agrees_with_fp32_tile(dev, kind, N, M, R, K):
     g = torch.Generator(device=dev).manual_seed(3)
     xh = torch.randn((20000, basis.B), generator=g, device=dev)
     a = [t.clone() for t in rsc.rsc_omp_encode(h, xh, K)]
-    rsc.rsc_set_tile(h, "16")
+    rsc.rsc_set_tile(h, tile)
     b = rsc.rsc_omp_encode(h, xh, K)
-    same = ((a[0] == b[0]) & (a[1] == b[1])).all(dim=1)
-    print("screen vs tile", kind, N, int((~same).sum()), flush=True)
-    assert int((~same).sum()) <= 20     # 99.9%; a handful of ties in 1e5 steps are expected
-    assert float((a[2] - b[2])[same].abs().max()) <= 1e-4 * float(b[2].abs().max())
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
     h.close()
 
 
@@ -158,18 +157,19 @@ def test_autotune_refuses_annular_beyond_four(dev):
         rsc.rsc_autotune_encode(h, x, 5)
 
 
-@pytest.mark.parametrize("kind,N,K,P", [("grid", 15, 1, 1), ("grid", 15, 2, 33), ("grid", 11, 1, 5003), ("annular", 11, 1, 700)])
-def test_classify_takes_the_smallest_error(dev, kind, N, K, P):
+@pytest.mark.parametrize("kind,N,K,P,M", [("grid", 15, 1, 1, 20), ("grid", 15, 2, 33, 20), ("grid", 11, 1, 5003, 20),
+                                          ("annular", 11, 1, 700, 20), ("grid", 15, 1, 3001, 97), ("grid", 11, 4, 999, 60)])
+def test_classify_takes_the_smallest_error(dev, kind, N, K, P, M):
     """Labels and errors that the screened encoder writes itself are those of one pursuit per class:
     the smallest squared residual norm, the first class on equal ones (the first two share a
-    dictionary), bit for bit (M K < 64: the same launches)."""
+    dictionary), bit for bit."""
     from paper_1806_04374_amd import rsc
     basis, _ = _make(kind, N)
     rng = np.random.default_rng([N, K, P])
     hs = []
     for c in range(4):
         if c != 1:
-            d = rng.standard_normal((20 + c, basis.B)).astype(np.float32)
+            d = rng.standard_normal((M + c, basis.B)).astype(np.float32)
         h = _make(kind, N)[1] if c < 3 or kind == "annular" else rsc.rsc_create(N, basis.S, basis.T, prec="bf16")
         rsc.rsc_set_dictionary(h, d / np.linalg.norm(d, axis=1, keepdims=True), 48)
         hs.append(h)
