@@ -18,8 +18,9 @@ LIB = os.path.join(PKG, "librsc.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-# packed FP32 instructions are switched off for all device code
-DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# packed FP32 instructions are switched off for all device code; an expression whose value hangs on
+# the order of its parts' side effects is an error
+DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Werror=unsequenced"]
 
 SOURCES = [
     ("rsc_basis.cpp", "host"),

@@ -239,7 +239,10 @@ __device__ __forceinline__ int other_half(int x, int u) { return int(other_half(
 // Sum over the W lanes of a patch; bit-identical in all of them.
 template <int W>
 __device__ __forceinline__ float patch_sum(float x) {
-  if (W == 4) return (x = x + __shfl_xor(x, 16)) + __shfl_xor(x, 32);
+  if (W == 4) {
+    x = x + __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+  }
   float a = x, b = x;
   swap32(a, b);                                                    // [lo | lo], [hi | hi]
   return a + b;
