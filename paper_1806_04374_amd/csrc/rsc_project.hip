@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* 
   __shared__ v4f tile4[VPT * NTH];               // [32][NNC] used; the rest takes clamped copies
   __shared__ uint4 xb[3 * NS * 64];
   __shared__ int4 sPix[NS * 4];
-  __shared__ int infinite[2];                    // of this chunk and the next
+  __shared__ unsigned colmax[2][32];             // largest magnitudes per patch (as bits), of this chunk and the next
   const float* tile = reinterpret_cast<const float*>(tile4);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 31, u = lane >> 5;
   uint4 a[NS][3];
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* 
     for (int q = 0; q < 3; ++q) a[j][q] = pinv3[((w * 3 + q) * NS + j) * 64 + lane];
   // slots past the disk have zero operand parts: point them at disk pixel 0
   for (int i = t; i < 16 * NS; i += NTH) reinterpret_cast<int*>(sPix)[i] = pix[i < n_pix ? i : 0];
-  if (t == 0) infinite[0] = infinite[1] = 0;
+  if (t < 64) colmax[t >> 5][t & 31] = 0u;
   __syncthreads();
   int vi[VPT];
 #pragma unroll
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* 
       for (int i = t; i < kProjRegPatches * NNC; i += NTH) tw[i] = i < tail * NNC ? src[i] : 0.f;
     }
     __syncthreads();   // (every wave is past the previous chunk's products)
-    if (t == 0) infinite[k & 1 ^ 1] = 0;
+    if (t < 32) colmax[k & 1 ^ 1][t] = 0u;
     if (nfull > 0) {
       const int64_t nx = c + gridDim.x, cn = nx < nfull ? nx : (c < nfull ? c : nfull - 1);
       const v4f* s4 = reinterpret_cast<const v4f*>(patches + cn * kProjRegPatches * NNC);
@@ -381,6 +381,7 @@ __global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* 
       for (int v = 0; v < VPT; ++v) nxt[v] = s4[vi[v]];
     }
     // wave w splits steps w, w + NT, ...
+    float vmax = 0.f;
 #pragma unroll 1
     for (int j = w; j < NS; j += NT) {
       const int4 p0 = sPix[j * 4 + u * 2], p1 = sPix[j * 4 + u * 2 + 1];
@@ -391,12 +392,13 @@ __global__ __launch_bounds__(64 * NT, 2) void project_split_kernel(const float* 
       xb[j * 64 + lane] = hi;
       xb[(NS + j) * 64 + lane] = mid;
       xb[(2 * NS + j) * 64 + lane] = lo;
-      if (any_infinite(v)) infinite[k & 1] = 1;
+      vmax = largest(v, vmax);
     }
+    atomicMax(&colmax[k & 1][col], __float_as_uint(vmax));
     __syncthreads();
     f32x16 acc = contract_split3<NS>(a, xb, lane);
-    if (infinite[k & 1]) {
-      // an infinite pixel in the chunk: the FP32 products
+    if (__any(needs_fp32(__uint_as_float(colmax[k & 1][col])))) {
+      // an infinite pixel or a tiny patch in the chunk: the FP32 products
       const int64_t p = c * kProjRegPatches + col;
       const float* src = patches + (p < nfull * kProjRegPatches + tail ? p : 0) * NNC;
 #pragma unroll

@@ -576,7 +576,7 @@ __global__ __launch_bounds__(64 * NT, 2) void synth_split_kernel(const float* __
   __shared__ v4f xs4[VPT * NTH];                 // [32][BB] used; the rest takes clamped copies
   __shared__ uint4 xb[3 * NS * 64];
   __shared__ v4f st4[kSynMP * NNC / 4];          // [32 patches][NNC]
-  __shared__ int infinite[2];                    // of this chunk and the next
+  __shared__ unsigned colmax[2][32];             // largest magnitudes per patch (as bits), of this chunk and the next
   float* st = reinterpret_cast<float*>(st4);
   float* xs = reinterpret_cast<float*>(xs4);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, col = lane & 31, u = lane >> 5;
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(64 * NT, 2) void synth_split_kernel(const float* __
   int vi[VPT];
 #pragma unroll
   for (int v = 0; v < VPT; ++v) vi[v] = t + NTH * v < NV ? t + NTH * v : NV - 1;
-  if (t == 0) infinite[0] = infinite[1] = 0;
+  if (t < 64) colmax[t >> 5][t & 31] = 0u;
   __syncthreads();
   const int64_t nfull = P / kSynMP, nchunk = (P + kSynMP - 1) / kSynMP;
   const int tail = int(P - nfull * kSynMP);
@@ -612,8 +612,9 @@ __global__ __launch_bounds__(64 * NT, 2) void synth_split_kernel(const float* __
       for (int i = t; i < kSynMP * BB; i += NTH) xs[i] = i < tail * BB ? xhat[c * kSynMP * BB + i] : 0.f;
     }
     __syncthreads();   // (every wave is past the previous chunk's products)
-    if (t == 0) infinite[k & 1 ^ 1] = 0;
+    if (t < 32) colmax[k & 1 ^ 1][t] = 0u;
     fetch(c + gridDim.x);
+    float vmax = 0.f;
 #pragma unroll 1
     for (int j = w; j < NS; j += NT) {
       float v[8];
@@ -627,11 +628,12 @@ __global__ __launch_bounds__(64 * NT, 2) void synth_split_kernel(const float* __
       xb[j * 64 + lane] = hi;
       xb[(NS + j) * 64 + lane] = mid;
       xb[(2 * NS + j) * 64 + lane] = lo;
-      if (any_infinite(v)) infinite[k & 1] = 1;
+      vmax = largest(v, vmax);
     }
+    atomicMax(&colmax[k & 1][col], __float_as_uint(vmax));
     __syncthreads();
     f32x16 acc = contract_split3<NS>(a, xb, lane);
-    if (infinite[k & 1]) {   // an infinite coordinate in the chunk: the FP32 products
+    if (__any(needs_fp32(__uint_as_float(colmax[k & 1][col])))) {   // the FP32 products
       const int64_t p = c * kSynMP + col;
       const float* src = xhat + (p < P ? p : 0) * BB;
 #pragma unroll

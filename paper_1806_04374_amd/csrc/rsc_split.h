@@ -35,13 +35,17 @@ __device__ __forceinline__ void split3(const float (&v)[8], uint4& hi, uint4& mi
   lo = uint4{pack(l[0], l[1]), pack(l[2], l[3]), pack(l[4], l[5]), pack(l[6], l[7])};
 }
 
-// Whether any of the eight values is infinite: its remainders are NaN, so chunks that hold one are
-// done in plain FP32.
-__device__ __forceinline__ bool any_infinite(const float (&v)[8]) {
-  float m = fabsf(v[0]);
+// The parts hold every bit of a value only if its last part is a normal number: values below about
+// 2^-110 lose low bits, and an infinite one leaves NaN remainders.  So each column (patch) of a
+// chunk keeps its largest magnitude, and a chunk is done in plain FP32 where a column's is
+// infinite, or so small that what its values lose (2^-126 at most) is more than 2^-26 of it.
+__device__ __forceinline__ float largest(const float (&v)[8], float m) {
 #pragma unroll
-  for (int i = 1; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
-  return m == __builtin_inff();
+  for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+  return m;
+}
+__device__ __forceinline__ bool needs_fp32(float largest) {
+  return largest == __builtin_inff() || (largest > 0.f && largest < 0x1p-100f);
 }
 
 // Sum over NS steps of a[step] (three parts) times the operand in LDS, xb: [3][NS][64].  The five

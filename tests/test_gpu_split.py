@@ -88,3 +88,27 @@ def test_infinite_values_as_in_fp32(dev):
     assert np.array_equal(px[3][disk][big], np.where(f[big] > 0, -np.inf, np.inf))
     assert np.isfinite(np.delete(px, 3, axis=0)).all()
     h.close()
+
+
+@pytest.mark.parametrize("kind,N", [("grid", 15), ("annular", 15), ("annular", 11)])
+@pytest.mark.parametrize("power", [-115, -105, -95, 100])
+def test_small_and_large_patches(dev, kind, N, power):
+    """Patches whose values are too small for three whole BF16 parts (their last part would be below the
+    normal numbers) keep the accuracy of the others, alone in a chunk of ordinary ones and in whole
+    chunks; scaling by a power of two changes nothing above that range."""
+    from paper_1806_04374_amd import rsc
+    basis, h, disk = _make(kind, N)
+    rng = np.random.default_rng(N)
+    scale = np.ldexp(1.0, np.where((np.arange(100) == 5) | (np.arange(100) >= 40), power, 0)).astype(np.float32)
+    xh = rng.standard_normal((100, basis.B)).astype(np.float32) * scale[:, None]
+    px = rsc.rsc_synthesize_hat(h, torch.from_numpy(xh).to(dev)).cpu().numpy().reshape(100, -1)[:, disk]
+    want = xh.astype(np.float64) @ basis.phi.T
+    for p in range(100):
+        assert _rel(px[p], want[p]) <= 2 * REL, p
+    if N == 15:
+        x = rng.standard_normal((100, 15, 15)).astype(np.float32) * scale[:, None, None]
+        out = rsc.rsc_project(h, torch.from_numpy(x).to(dev)).cpu().numpy()
+        want = x.reshape(100, -1)[:, disk].astype(np.float64) @ basis.pinv.T
+        for p in range(100):
+            assert _rel(out[p], want[p]) <= 2 * REL, p
+    h.close()
