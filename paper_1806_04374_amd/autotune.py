@@ -1,10 +1,11 @@
 """Launch-shape autotuning with a JSON cache.
 
-The first time a (geometry, dictionary size, angle grid, K, precision, device) combination is
-seen, the encoder's usable launch shapes are timed on a sample of the caller's own
+The first time a (basis, geometry, dictionary size, angle grid, K, precision, device) combination
+is seen, the encoder's usable launch shapes are timed on a sample of the caller's own
 coordinates (rsc_autotune_encode) and the fastest is stored; later calls apply the
-cached choice without timing.  Cache file: $RSC_AUTOTUNE_CACHE, else
-~/.cache/rsc_autotune.json.
+cached choice without timing.  A choice that was made before the library had its present form of
+the encoder (the form that "auto" takes is not among the timed ones) is timed again.  Cache file:
+$RSC_AUTOTUNE_CACHE, else ~/.cache/rsc_autotune.json.
 """
 from __future__ import annotations
 
@@ -22,7 +23,8 @@ def cache_path() -> str:
 def key(h: rsc.Handle, K: int) -> str:
     import torch
     name = torch.cuda.get_device_name(0).replace(" ", "_") if torch.cuda.is_available() else "cpu"
-    return f"N{h.N}-S{h.S}-T{h.T}-M{h.M}-R{h.R}-K{K}-{getattr(h, 'prec', 'fp32')}-{name}"
+    basis = "annular" if hasattr(h, "Ts") else "grid"
+    return f"{basis}-N{h.N}-S{h.S}-T{h.T}-B{h.B}-M{h.M}-R{h.R}-K{K}-{getattr(h, 'prec', 'fp32')}-{name}"
 
 
 def _load(path):
@@ -44,8 +46,13 @@ def tune(h: rsc.Handle, xhat_sample, K: int, reps: int = 5, path: str | None = N
     db = _load(path)
     k = key(h, K)
     if not force and k in db:
-        rsc.rsc_set_launch(h, db[k]["tile"], db[k]["blocks_per_cu"])
-        return dict(db[k], cached=True)
+        tile, bpc = rsc.rsc_get_launch(h)
+        rsc.rsc_set_launch(h, "auto", 0)
+        form, _ = rsc.rsc_encode_info(h, K)
+        rsc.rsc_set_launch(h, tile, bpc)
+        if form in {c["tile"] for c in db[k].get("candidates", [])}:
+            rsc.rsc_set_launch(h, db[k]["tile"], db[k]["blocks_per_cu"])
+            return dict(db[k], cached=True)
     rows = rsc.rsc_autotune_encode(h, xhat_sample, K, reps)
     tile, bpc = rsc.rsc_get_launch(h)
     entry = {"tile": tile, "blocks_per_cu": bpc, "sample_patches": int(xhat_sample.shape[0]),
