@@ -593,6 +593,8 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
           const f32x16 a1 = k1 < NJ ? P::mfma(Ag[(k1 < NJ ? k1 : k0) * 64], r16[k1 < NJ ? k1 : k0], zro) : zro;
 #pragma unroll
           for (int a = 0; a < 16; ++a) opk[a][j] = pack2<P>(a0[a], a1[a]);
+          // with one angle tile the scheduler would keep all eight accumulators (128 registers)
+          if (RT == 1) __builtin_amdgcn_sched_barrier(0);
         }
         const int ab = AG * g;
         // stage 2 by (atom, angle tile) units, one unit in flight: the next unit's
@@ -778,30 +780,19 @@ __global__ __launch_bounds__(512, 2) void encode_screen_kernel(ScreenParams prm)
       // maximum.  max(|E| + |O|) is bit for bit the largest rounded |E + O| or |E - O|, so the
       // scores are compared with it for equality; rows past the valid angles score 0 and come
       // last.  The rows ascend with the register in each half-wave: searched from the last.
-      int rs = 0x7fffffff;
+      // rc: 32 (half of the angles or tile) + 8 (i / 4) + i % 4, a constant of the instruction
+      int rc = -1;
       float cval = 0.f;
-      if (SPLIT) {
-        const int HALF = R / 2;
 #pragma unroll
-        for (int h = 1; h >= 0; --h)
+      for (int t = SPLIT ? 1 : FT - 1; t >= 0; --t)
 #pragma unroll
-          for (int i = 15; i >= 0; --i) {
-            const float s = h == 0 ? E[0][i] + O[i] : E[0][i] - O[i];
-            const bool eq = fabsf(s) == best;
-            rs = eq ? 8 * (i / 4) + (i % 4) + 4 * u + h * HALF : rs;
-            cval = eq ? s : cval;
-          }
-      } else {
-#pragma unroll
-        for (int t = FT - 1; t >= 0; --t)
-#pragma unroll
-          for (int i = 15; i >= 0; --i) {
-            const float s = E[t][i];
-            const bool eq = fabsf(s) == best;
-            rs = eq ? 32 * t + 8 * (i / 4) + (i % 4) + 4 * u : rs;
-            cval = eq ? s : cval;
-          }
-      }
+        for (int i = 15; i >= 0; --i) {
+          const float s = !SPLIT ? E[t % FT][i] : t == 0 ? E[0][i] + O[i] : E[0][i] - O[i];
+          const bool eq = fabsf(s) == best;
+          rc = eq ? 32 * t + 8 * (i / 4) + i % 4 : rc;
+          cval = eq ? s : cval;
+        }
+      int rs = rc < 0 ? 0x7fffffff : SPLIT ? (rc & 31) + 4 * u + (rc >> 5) * (R / 2) : rc + 4 * u;
       {
         const float ov = other_half(cval, u);
         const int oc = other_half(rs, u);
