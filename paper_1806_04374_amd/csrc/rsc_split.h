@@ -2,9 +2,11 @@
 //   x = hi + mid + lo  (exact for a 24-bit significand),
 // and the six products down to 2^-16 of the largest are accumulated in FP32,
 //   hi hi, hi mid, mid hi, hi lo, lo hi, mid mid.
-// The dropped products are at most 2^-24 of |a||x|.  Six v_mfma_f32_32x32x16_bf16 take 192 cycles per
-// 16 terms, eight v_mfma_f32_32x32x2f32 512, and the result is closer to the 64-bit one: at 15x15
-// the projection's relative error is 0.8e-7 against 2.3e-7 (a chain of 89 FP32 roundings).
+// The operand's parts are rounded (mid at most 2^-8 of it, lo 2^-17), the data's truncated (2^-7 and
+// 2^-15), so the three dropped products add up to at most 2^-22 of |a||x| (2^-26.5 on average).  Six
+// v_mfma_f32_32x32x16_bf16 take 192 cycles per 16 terms, eight v_mfma_f32_32x32x2f32 512, and the result
+// is closer to the 64-bit one: at 15x15 the projection's relative error is 0.8e-7 against 2.3e-7 (a
+// chain of 89 FP32 roundings).
 //
 // Operand layout of one 16-term step: lane l supplies terms 8 (l / 32) + i, i = 0..7, of row
 // (or column) l % 32.

@@ -1,8 +1,8 @@
 """The 15x15 patch projection and the synthesis in three BF16 parts, against the FP64 basis.
 
-Error: the parts hold 24 significant bits, the dropped products are below 2^-24 of |a||x| each and
-the sum is rounded at its full size once per 16 terms, so a coordinate is within a few 2^-24 of
-sum |a||x|; sqrt-summed over the terms that is below 3e-7 of the 2-norm here (FP32 products in
+Error: the parts hold 24 significant bits, the dropped products add up to at most 2^-22 of |a||x| (a
+twentieth of that on average, with either sign) and the sum is rounded at its full size once per 16
+terms, so a coordinate is within a few 2^-24 of sum |a||x| on average; sqrt-summed over the terms that is below 3e-7 of the 2-norm here (FP32 products in
 a chain: 2.5e-7 measured, these: 0.9e-7), asserted at 3e-7.  Wide ranges, whole and part chunks,
 and chunks that hold an infinite value, which take FP32 products."""
 import numpy as np
