@@ -233,10 +233,10 @@ rsc_status rsc_encode_info(const rsc_handle* h, int K, int* tile, double* mfma_f
 rsc_status rsc_get_launch(const rsc_handle* h, int* tile, int* blocks_per_cu);
 
 /*
- * Autotuner: times rsc_omp_encode on a representative sample for every usable form (the
- * screened one in place of RSC_TILE_16 where there is one) and blocks_per_cu = 1..4 (median of
- * reps runs, HIP events on the stream),
- * then keeps the fastest in the handle.  Blocking; not for a hot loop.
+ * Autotuner: times rsc_omp_encode on a representative sample for every usable tile shape (where
+ * there is a screened form, for it and for the tile with the same codes, which is the faster one
+ * where the screen cannot leave atoms out) and blocks_per_cu = 1..4 (median of reps runs, HIP
+ * events on the stream), then keeps the fastest in the handle.  Blocking; not for a hot loop.
  *   xhat              device [P, B] sample, P >= 1
  *   atom, angle, coef device [P, K] scratch outputs (overwritten)
  *   reps              1..100

@@ -859,11 +859,15 @@ rsc_status rsc_autotune_encode(rsc_handle* h, const float* xhat, int64_t P, int 
   if (rsc_status f = dict_before(h, stream)) return f;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool lp = h->prec != RSC_FP32;
-  // FP32 handles: the library's screened form (RSC_TILE_AUTO) where there is one, and otherwise
-  // every FP32 tile shape; 16-bit handles have one form
-  const bool screened = rsc::screen_usable(h->dev, K);
-  int tiles[2] = {lp ? RSC_TILE_32 : screened ? RSC_TILE_AUTO : RSC_TILE_16, RSC_TILE_32};
-  const int ntiles = (!lp && rsc::tile32_usable(h->dev, K)) ? 2 : 1;
+  // FP32 handles: the screened form (RSC_TILE_AUTO) where there is one and the full form with the same
+  // codes, which is ahead where the screen leaves most atoms in: a dictionary of near copies, or
+  // low-contrast windows with atoms of no mean (100,000 15x15 windows, M = 128, K = 6, contrast 0.01
+  // of the mean: 5.1 ms screened, 1.5 full; contrast 0.3: 0.54 and 1.49).  Without a screen every FP32
+  // tile shape; 16-bit handles have one form.
+  const bool screened = rsc::screen_usable(h->dev, K), t32 = rsc::tile32_usable(h->dev, K);
+  int tiles[2] = {lp ? RSC_TILE_32 : screened ? RSC_TILE_AUTO : RSC_TILE_16,
+                  screened ? encoder_tile(h, RSC_TILE_AUTO, K) : RSC_TILE_32};
+  const int ntiles = !lp && (screened || t32) ? 2 : 1;
   auto run = [&](int tile) {
     return lp || (screened && tile == RSC_TILE_AUTO)
                ? encode_screened(h, xhat, P, K, atom, angle, coef, nullptr, stream)

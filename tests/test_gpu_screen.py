@@ -157,6 +157,47 @@ def test_autotune_refuses_annular_beyond_four(dev):
         rsc.rsc_autotune_encode(h, x, 5)
 
 
+@pytest.mark.parametrize("kind,N,prec,R,K,tiles", [("grid", 11, "fp32", 64, 4, ["auto", "32"]), ("grid", 11, "fp32", 30, 4, ["auto", "16"]),
+                                                  ("grid", 15, "fp32", 64, 2, ["auto", "16"]), ("annular", 11, "fp32", 64, 2, ["auto", "16"]),
+                                                  ("annular", 15, "fp32", 64, 2, ["16"]), ("grid", 11, "bf16", 64, 4, ["32"])])
+def test_autotune_times_both_forms(dev, kind, N, prec, R, K, tiles):
+    """Where the library has a screened form the autotuner times it against the full form with the
+    same codes, so whichever it keeps, the codes are the same."""
+    from paper_1806_04374_amd import rsc
+    basis, h = _make(kind, N)
+    if prec != "fp32":
+        h = rsc.rsc_create(N, basis.S, basis.T, prec=prec)
+    d = np.random.default_rng(2).standard_normal((24, basis.B)).astype(np.float32)
+    rsc.rsc_set_dictionary(h, d / np.linalg.norm(d, axis=1, keepdims=True), R)
+    x = torch.randn((3000, basis.B), generator=torch.Generator(device=dev).manual_seed(1), device=dev)
+    before = [t.clone() for t in rsc.rsc_omp_encode(h, x, K)]
+    rows = rsc.rsc_autotune_encode(h, x, K, reps=1)
+    assert [r[0] for r in rows] == [t for t in tiles for _ in range(4)]
+    assert rsc.rsc_get_launch(h)[0] in tiles
+    for t in tiles:
+        rsc.rsc_set_launch(h, t, 1)
+        for a, b in zip(before, rsc.rsc_omp_encode(h, x, K)):
+            assert torch.equal(a, b)
+    h.close()
+
+
+def test_autotune_keeps_the_full_form_for_low_contrast(dev):
+    """Windows whose contrast is 0.01 of their mean, coded with atoms of no mean: nearly every atom is a
+    candidate of the screen, and the full form is more than three times as fast."""
+    from paper_1806_04374_amd import rsc
+    basis, h = _make("grid", 15)
+    const = basis.pinv.sum(axis=1)
+    const /= np.linalg.norm(const)
+    d = np.random.default_rng(1).standard_normal((128, basis.B))
+    d -= (d @ const)[:, None] * const
+    rsc.rsc_set_dictionary(h, (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32), 64)
+    x = torch.randn((60000, basis.B), generator=torch.Generator(device=dev).manual_seed(1), device=dev)
+    x = x / x.norm(dim=1, keepdim=True) * 0.01 + torch.from_numpy(const).to(dev).float()
+    rsc.rsc_autotune_encode(h, x, 4, reps=3)
+    assert rsc.rsc_get_launch(h)[0] == "16"
+    h.close()
+
+
 @pytest.mark.parametrize("kind,N,K,P,M", [("grid", 15, 1, 1, 20), ("grid", 15, 2, 33, 20), ("grid", 11, 1, 5003, 20),
                                           ("annular", 11, 1, 700, 20), ("grid", 15, 1, 3001, 97), ("grid", 11, 4, 999, 60)])
 def test_classify_takes_the_smallest_error(dev, kind, N, K, P, M):
